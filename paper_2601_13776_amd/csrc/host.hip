@@ -491,46 +491,65 @@ struct Arena {
 };
 
 // fp32 GEMM work of one launch: one item per product, one GemmTile per
-// 64 x 64 output tile (consecutive tiles of a product share its item).  In
-// the workspace: the items, then the tiles.
-static_assert(sizeof(GemmItem) % 8 == 0 && sizeof(GemmItem) == 8 * 8 + 14 * 8 + 18 * 4,
+// output tile (consecutive tiles of a product share its item).  In the
+// workspace: the items, then the tiles.
+static_assert(sizeof(GemmItem) % 8 == 0 && sizeof(GemmItem) == 8 * 8 + 14 * 8 + 16 * 4,
               "GemmItem must have no padding: items are compared bytewise");
-// Products added whole (add_all) get their tiles at finalize().  (128 x 128
-// tiles for lists of large products were measured 5-30% slower with this
-// kernel's register-staged loads, so every list uses 64 x 64.)
+// Tile edge of a list whose products make n128 tiles of 128: those halve
+// the LDS traffic and splitting work per product, but a 64-tile list has
+// four times the tiles to fill the 256 compute units with (2048 x 1024,
+// K = 512, two pieces: 16.2 us with 128 tiles of 128, 14.2 us with 512 of
+// 64; 2048^3: 61 us with 256 of 128, 80 us with 1024 of 64).
+constexpr int64_t kTile128Min = 256;
+inline int gemm_tile_edge(int64_t n128) { return n128 >= kTile128Min ? 128 : 64; }
+inline int64_t tiles_of(int64_t rows, int edge) { return (rows + edge - 1) / edge; }
+// Products added whole (add_all) get their tiles at finalize().
 struct GemmList {
   std::vector<GemmItem> items;
   std::vector<GemmTile> tiles;
   std::vector<int32_t> pending;   // add_all products without tiles yet
-  int64_t pending64 = 0;          // their tile count
+  int64_t pending64 = 0;          // their count of 64-tiles
   GemmItem last{};   // items.back() with its tile and mirror fields cleared
-  int64_t n_km = 0;  // trailing tiles for the k-major instantiation (set by put)
+  GemmRun run{GEMM_BF16X3, 64, {0, 0, 0}};
+  // at most this many tiles (the count with 64-tiles)
   size_t size() const { return tiles.size() + (size_t)pending64; }
   void clear() {
     items.clear();
     tiles.clear();
     pending.clear();
     pending64 = 0;
-    n_km = 0;
   }
-  // single-pair products with both operands stored k-major
-  static bool kmajor(const GemmItem& it) { return it.a_trans && it.b_trans && it.K2 <= 0 && it.pair_count == 0; }
-  // moves the k-major tiles to the end (stable: each part keeps its order)
-  void partition_km() {
-    auto it = std::stable_partition(tiles.begin(), tiles.end(),
-                                    [&](const GemmTile& t) { return !kmajor(items[t.item]); });
-    n_km = tiles.end() - it;
+  // how every operand of the product is stored
+  static GemmMode mode(const GemmItem& it) {
+    if (it.a_dtype != ORTH_F32 || it.b_dtype != ORTH_F32) return GEMM_ANY;
+    if (it.trans == 0) return GEMM_ROWS;   // further pairs are row-major too
+    if (it.trans == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
+      return GEMM_KMAJOR;
+    return GEMM_ANY;
+  }
+  // tiles of one storage after the other (stable: each part keeps its order)
+  void partition() {
+    finalize();
+    std::stable_sort(tiles.begin(), tiles.end(), [&](const GemmTile& a, const GemmTile& b) {
+      return mode(items[a.item]) < mode(items[b.item]);
+    });
+    run.n[0] = run.n[1] = run.n[2] = 0;
+    for (const GemmTile& t : tiles) ++run.n[mode(items[t.item])];
   }
   void finalize() {
+    if (pending.empty()) return;
+    int64_t n128 = 0;
+    for (int32_t idx : pending) n128 += tiles_of(items[idx].M, 128) * tiles_of(items[idx].N, 128);
+    run.tile = gemm_tile_edge(n128);
     for (int32_t idx : pending)
-      for (int a = 0; a < (items[idx].M + 63) / 64; ++a)
-        for (int b = 0; b < (items[idx].N + 63) / 64; ++b) tiles.push_back(GemmTile{idx, a, b, 0});
+      for (int a = 0; a < tiles_of(items[idx].M, run.tile); ++a)
+        for (int b = 0; b < tiles_of(items[idx].N, run.tile); ++b) tiles.push_back(GemmTile{idx, a, b, 0});
     pending.clear();
     pending64 = 0;
   }
-  // one tile, given as a whole item with its ti, tj (and mirror for an
-  // off-diagonal tile); it shares the previous tile's item when the rest
-  // matches
+  // one tile (edge run.tile), given as a whole item with its ti, tj (and
+  // mirror for an off-diagonal tile); it shares the previous tile's item
+  // when the rest matches
   void push_back(const GemmItem& g) {
     GemmItem k = g;
     k.ti = k.tj = 0;
@@ -550,7 +569,7 @@ struct GemmList {
     last = k;
     last.mirror = 0;
     pending.push_back((int32_t)items.size() - 1);
-    pending64 += (int64_t)((proto.M + 63) / 64) * ((proto.N + 63) / 64);
+    pending64 += tiles_of(proto.M, 64) * tiles_of(proto.N, 64);
   }
   size_t items_bytes() const { return align_up(items.size() * sizeof(GemmItem)); }
   // workspace bytes for at most n tiles, each of its own product
@@ -558,12 +577,10 @@ struct GemmList {
   size_t bytes() const { return items_bytes() + align_up(tiles.size() * sizeof(GemmTile)); }
 };
 
-// Tiles of the products added whole, and the k-major tiles moved to the
-// end: a list is sealed once its plan is complete, before any upload.
-void seal(GemmList& g) {
-  g.finalize();
-  g.partition_km();
-}
+// Tiles of the products added whole, and the tiles ordered by their
+// operands' storage: a list is sealed once its plan is complete, before any
+// upload.
+void seal(GemmList& g) { g.partition(); }
 void put(TableImage& img, size_t off, const GemmList& g) {
   img.add(off, g.items.data(), g.items.size() * sizeof(GemmItem));
   img.add(off + g.items_bytes(), g.tiles.data(), g.tiles.size() * sizeof(GemmTile));
@@ -589,9 +606,15 @@ void longest_first(GemmList& g) {
 hipError_t launch_list(const unsigned char* ws, size_t off, const GemmList& g, const char* name, hipStream_t s,
                        int step = 0, const GemmPair* pairs = nullptr) {
   return launch_gemm_f32(reinterpret_cast<const GemmItem*>(ws + off),
-                         reinterpret_cast<const GemmTile*>(ws + off + g.items_bytes()), (int)g.size(), name, s,
-                         step, pairs, (int)g.n_km);
+                         reinterpret_cast<const GemmTile*>(ws + off + g.items_bytes()), g.run, name, s, step, pairs);
 }
+
+// Exponents of operands of known range (GEMM_F16X2).  Iterates are scaled
+// to at most 1 (Frobenius) or to a largest singular value below sqrt(3)
+// where the iteration converges (spectral), E and the exponential map's
+// Ahat likewise, so 2^14 times their values stay below half's 65504.
+// Without pre-scaling nothing is known, and three bfloat16 pieces are used.
+constexpr int kIterExp = 14;
 
 }  // namespace
 
@@ -642,7 +665,8 @@ void log_ortho_plan(const char* entry, const OrthoPlan& P, const orth_bjorck_opt
       log_line("%s: bf16 %d-tiles per step: %zu Gram + %zu update", entry, cls ? 256 : 128,
                P.tabs[cls][TAB_GRAM].size(), P.tabs[cls][TAB_UPDATE].size());
   if (P.f32_gram.size())
-    log_line("%s: fp32 64-tiles per step: %zu Gram + %zu update", entry, P.f32_gram.size(), P.f32_update[0].size());
+    log_line("%s: fp32 tiles per step: %zu Gram of %d + %zu update of %d", entry, P.f32_gram.size(), P.f32_gram.run.tile,
+             P.f32_update[0].size(), P.f32_update[0].run.tile);
   log_line("%s: workspace %zu bytes (tables %zu); outputs holding the fp32 iterate: %d", entry, P.total_bytes,
            P.table_bytes, P.n_out_iter);
   if (log_level() >= 3)
@@ -815,6 +839,19 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
 
   auto dev = [&](size_t off) -> unsigned char* { return ws ? ws + off : nullptr; };
 
+  // fp32 products: tile edges and pieces of the step's two lists
+  const bool two_pieces = o->prescale != ORTH_PRESCALE_NONE;
+  int64_t g128 = 0, u128 = 0;
+  for (const MatPlan& q : P.mp)
+    if (q.bucket == TILED_F32) {
+      const int64_t tn = tiles_of(q.Np, 128);
+      g128 += tn * (tn + 1) / 2;
+      u128 += tiles_of(q.Mp, 128) * tn;
+    }
+  const GemmSplit split = two_pieces ? GEMM_F16X2 : GEMM_BF16X3;
+  P.f32_gram.run = GemmRun{split, gemm_tile_edge(g128), {0, 0, 0}};
+  P.f32_update[0].run = P.f32_update[1].run = GemmRun{split, gemm_tile_edge(u128), {0, 0, 0}};
+
   // per-matrix buffers and descriptors
   int part_base = 0;
   int64_t u_off = 0;   // this matrix's cached vector in the packed array
@@ -902,10 +939,10 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
       for (int b = 0; b < q.Np / 64; ++b) P.scale_items.push_back(TileItem{tiled_idx, a, b, 0});
 
     if (q.bucket == TILED_F32) {
-      const int tn = q.Np / 64, tm = q.Mp / 64;
+      const int ge = P.f32_gram.run.tile, ue = P.f32_update[0].run.tile;
       std::vector<TileItem> gt, ut;
-      grouped_tiles(tiled_idx, tn, tn, 4, true, gt);
-      grouped_tiles(tiled_idx, tm, tn, 4, false, ut);
+      grouped_tiles(tiled_idx, (int)tiles_of(q.Np, ge), (int)tiles_of(q.Np, ge), 4, true, gt);
+      grouped_tiles(tiled_idx, (int)tiles_of(q.Mp, ue), (int)tiles_of(q.Np, ue), 4, false, ut);
       for (auto& g : gt) {
         GemmItem gi{};
         gi.A = t.xt;
@@ -918,6 +955,7 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
         gi.ti = g.ti;
         gi.tj = g.tj;
         gi.a_dtype = gi.b_dtype = ORTH_F32;
+        gi.exps = two_pieces ? gemm_exps(kIterExp, kIterExp) : 0;
         gi.epi = EPI_GRAM_E;
         gi.mirror = g.ti != g.tj;
         P.f32_gram.push_back(gi);
@@ -941,6 +979,7 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
           gi.ti = u.ti;
           gi.tj = u.tj;
           gi.a_dtype = gi.b_dtype = ORTH_F32;
+          gi.exps = two_pieces ? gemm_exps(kIterExp, kIterExp) : 0;
           gi.epi = EPI_UPDATE;
           gi.beta = o->beta;
           P.f32_update[par].push_back(gi);
@@ -1399,7 +1438,7 @@ void build_conv_vjp_plan(const orth_conv_vjp_desc* d, int32_t n, int32_t dtype, 
             GemmItem gd{};
             gd.A = Ts[q + 1];
             gd.B = D;
-            gd.a_trans = gd.b_trans = 1;
+            gd.trans = GEMM_A_TRANS | GEMM_B_TRANS;
             gd.lda = gd.ldb = c;
             gd.K = h1 * w1 * og;
             gd.M = gd.N = c;
@@ -1416,7 +1455,7 @@ void build_conv_vjp_plan(const orth_conv_vjp_desc* d, int32_t n, int32_t dtype, 
           GemmItem gd{};
           gd.A = Ts[0];
           gd.B = D;
-          gd.a_trans = gd.b_trans = 1;
+          gd.trans = GEMM_A_TRANS | GEMM_B_TRANS;
           gd.lda = gd.ldb = c;
           gd.K = s * s * og;
           gd.M = gd.N = c;
@@ -1430,14 +1469,12 @@ void build_conv_vjp_plan(const orth_conv_vjp_desc* d, int32_t n, int32_t dtype, 
           gv.A = dP + (size_t)j * c * c;
           gv.lda = c;
           gv.B = proj + (size_t)j * c * h * esz;
-          gv.b_trans = 1;
+          gv.trans = GEMM_B_TRANS | GEMM_A2_TRANS | GEMM_B2_TRANS;
           gv.ldb = h;
           gv.K = c;
           gv.A2 = gv.A;
-          gv.a2_trans = 1;
           gv.lda2 = c;
           gv.B2 = gv.B;
-          gv.b2_trans = 1;
           gv.ldb2 = h;
           gv.K2 = c;
           gv.M = c;
@@ -1598,11 +1635,13 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
       g.ldc = C;
       g.dst2 = acc;
       g.ld2 = C;
+      g.exps = gemm_exps(kIterExp, kIterExp);
       g.beta = -1.f / k;
       g.epi = EPI_SERIES;
       gemm_tiles(g, P.steps[k - 2]);
     }
   }
+  for (auto& g : P.steps) g.run.split = GEMM_F16X2;   // |Ahat| is about 1
   P.total_bytes = align_up(A.off);
 }
 
@@ -1732,13 +1771,18 @@ struct VjpPlan {
   size_t off_f_gram = 0, off_f_upd = 0, off_b_s[2] = {}, off_b_upd[2] = {};
   size_t off_t_gram[2] = {}, off_t_upd[2] = {}, off_t_s[2][2] = {}, off_t_yu[2][2] = {};
   size_t off_partials = 0, off_inv = 0, off_dot = 0, off_status = 0;
+  // fp32 products: a slot per matrix for the largest upstream gradient, zero
+  // when the call starts
+  bool f32 = false;
+  std::vector<float> gmax;
+  size_t off_gmax = 0;
   size_t table_bytes = 0, total_bytes = 0;
 };
 
 void log_vjp_plan(const char* entry, const VjpPlan& P, int n) {
   if (log_level() < 1) return;
   log_line("%s: %d matrices (fused small: %zu + %zu), bf16 tiles per step: 128 %zu/%zu/%zu/%zu, 256 %zu/%zu/%zu/%zu "
-           "(Gram/update/S/gradient update), fp32 64-tiles %zu/%zu/%zu/%zu; workspace %zu bytes (tables %zu)",
+           "(Gram/update/S/gradient update), fp32 tiles %zu/%zu/%zu/%zu; workspace %zu bytes (tables %zu)",
            entry, n, P.small[0].size(), P.small[1].size(), P.t_gram[0].size(), P.t_upd[0].size(), P.t_s[0][0].size(),
            P.t_yu[0][0].size(), P.t_gram[1].size(), P.t_upd[1].size(), P.t_s[1][0].size(), P.t_yu[1][0].size(),
            P.f_gram.size(), P.f_upd.size(), P.b_s[0].size(), P.b_upd[0].size(), P.total_bytes, P.table_bytes);
@@ -1911,6 +1955,23 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
     }
   }
 
+  // fp32 products: tile edges and pieces (the gradient iterate is scaled to
+  // a largest value of 1 to 2, exponent 0: half's range leaves its growth
+  // over the steps a factor of 2^15)
+  const bool two_pieces = o->prescale != ORTH_PRESCALE_NONE;
+  const int x_exp = two_pieces ? kIterExp : 0;
+  int64_t g128 = 0, u128 = 0;
+  for (int i = 0; i < n; ++i)
+    if (P.bucket[i] == V_F32) {
+      const int64_t tn = tiles_of(P.mats[i].Np, 128);
+      g128 += tn * (tn + 1) / 2;
+      u128 += tiles_of(P.mats[i].Mp, 128) * tn;
+    }
+  const GemmSplit split = two_pieces ? GEMM_F16X2 : GEMM_BF16X3;
+  P.f_gram.run = P.b_s[0].run = P.b_s[1].run = GemmRun{split, gemm_tile_edge(g128), {0, 0, 0}};
+  P.f_upd.run = P.b_upd[0].run = P.b_upd[1].run = GemmRun{split, gemm_tile_edge(u128), {0, 0, 0}};
+  P.f32 = n_fu > 0;
+
   Arena A;
   P.off_mats = A.take(sizeof(TiledMat) * n);
   for (int k = 0; k < 2; ++k) P.off_small[k] = A.take(sizeof(SmallVjpMat) * P.small[k].size());
@@ -1932,6 +1993,8 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
   }
   for (int h = 0; h < 2; ++h) P.off_power[h] = A.take(sizeof(PowerItem) * n_pw[h]);
   P.off_bw = A.take(spectral ? sizeof(TiledMat) * n : 0);
+  P.gmax.assign(P.f32 ? n : 0, 0.f);
+  P.off_gmax = A.take(sizeof(float) * P.gmax.size());
   P.table_bytes = align_up(A.off);
   P.off_partials = A.take(sizeof(double) * n_part);
   P.off_inv = A.take(sizeof(float) * n);
@@ -2021,9 +2084,10 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
     t.gyt[1] = gyt1;
     t.s = sb;
     t.gy_final = T & 1;
-    const int tn = t.Np / 64, tm = t.Mp / 64;
-    for (int a = 0; a < tn; ++a)
-      for (int b = a; b < tn; ++b) {
+    const int ge = P.f_gram.run.tile, ue = P.f_upd.run.tile;
+    const int gn = (int)tiles_of(t.Np, ge), tn = (int)tiles_of(t.Np, ue), tm = (int)tiles_of(t.Mp, ue);
+    for (int a = 0; a < gn; ++a)
+      for (int b = a; b < gn; ++b) {
         GemmItem g{};
         g.A = xts;
         g.B = xts;
@@ -2037,6 +2101,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.ti = a;
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
+        g.exps = gemm_exps(x_exp, x_exp);
         g.epi = EPI_GRAM_E;
         g.mirror = a != b;
         P.f_gram.push_back(g);
@@ -2060,6 +2125,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.ti = a;
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
+          h.exps = gemm_exps(x_exp, 0, 0, x_exp);
           h.epi = EPI_NEG;
           h.mirror = a != b;
           P.b_s[par].push_back(h);
@@ -2089,6 +2155,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.ti = a;
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
+        g.exps = gemm_exps(x_exp, x_exp);
         g.epi = EPI_UPDATE;
         g.beta = o->beta;
         P.f_upd.push_back(g);
@@ -2119,6 +2186,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.ti = a;
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
+          h.exps = gemm_exps(0, x_exp, x_exp, 0);
           h.epi = EPI_UPDATE;
           h.beta = o->beta;
           P.b_upd[par].push_back(h);
@@ -2478,6 +2546,7 @@ int orth_orthogonalize_vjp_batched(const orth_vjp_mat* mats, int32_t n, const or
   put(img, P.off_power[0], P.power[0]);
   put(img, P.off_power[1], P.power[1]);
   put(img, P.off_bw, P.bw);
+  put(img, P.off_gmax, P.gmax);
   put(img, P.off_partial_items, P.partial_items);
   put(img, P.off_scale_items, P.scale_items);
   put(img, P.off_f_gram, P.f_gram);
@@ -2519,7 +2588,10 @@ int orth_orthogonalize_vjp_batched(const orth_vjp_mat* mats, int32_t n, const or
     if (rc) return rc;
   }
   // gradient recurrence, last step first
-  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, s));
+  float* gmax = P.f32 ? reinterpret_cast<float*>(ws + P.off_gmax) : nullptr;
+  if (gmax)
+    ORTH_HIP(launch_vjp_grad_max(tm, TI(P.off_partial_items), (int)P.partial_items.size(), opts->out_dtype, gmax, s));
+  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, gmax, s));
   for (int b = 0; b < T; ++b) {
     const int t = T - 1 - b, par = b & 1;
     ORTH_HIP(launch_list(ws, P.off_b_s[par], P.b_s[par], "vjp_s_f32", s, t));
@@ -2541,7 +2613,7 @@ int orth_orthogonalize_vjp_batched(const orth_vjp_mat* mats, int32_t n, const or
                              reinterpret_cast<const PowerItem*>(ws + P.off_power[1]), (int)P.power[1].size(),
                              opts->power_iters, opts->in_dtype, status, s));
   ORTH_HIP(launch_vjp_writeout(tm, TI(P.off_partial_items), (int)P.partial_items.size(), opts->in_dtype,
-                               opts->prescale, status, s));
+                               opts->prescale, status, gmax, s));
   ORTH_HIP(fk.join());
   if (opts->saved && status_dev)
     ORTH_HIP(hipMemcpyAsync(status_dev, status, sizeof(int32_t) * n, hipMemcpyDeviceToDevice, s));
@@ -2590,7 +2662,7 @@ int orth_build_conv_kernels_batched(const orth_conv_desc* descs, int32_t n, int3
   if (log_level() >= 1) {
     size_t tiles = P.proj_items.size();
     for (const auto& g : P.phase_gemm) tiles += g.size();
-    log_line("orth_build_conv_kernels_batched: %d layers, %zu groups, %zu block steps, %zu fp32 64-tiles; "
+    log_line("orth_build_conv_kernels_batched: %d layers, %zu groups, %zu block steps, %zu fp32 tiles; "
              "workspace %zu bytes (tables %zu)", n, P.groups.size(), P.phase_gemm.size(), tiles, P.total_bytes,
              P.table_bytes);
   }
@@ -2926,7 +2998,7 @@ void gram_check_items(const orth_check_args* a, float* out, GemmList& items) {
         g.ti = ti;
         g.tj = tj;
         g.a_dtype = g.b_dtype = a->mat_dtype;
-        g.a_trans = g.b_trans = tall ? 1 : 0;
+        g.trans = tall ? GEMM_A_TRANS | GEMM_B_TRANS : 0;
         g.epi = EPI_MAXDEV;
         g.red = out + i;
         items.push_back(g);

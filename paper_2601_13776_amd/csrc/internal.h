@@ -216,9 +216,9 @@ struct PowerItem {
   int32_t second;            // 0: v -> x, 1: x -> y
 };
 
-// Generic bounds-checked fp32 GEMM work item: C = A * B^T (+ A2 * B2^T)
-// over one 64 x 64 output tile, A logically M x K, B logically N x K, A2
-// M x K2, B2 N x K2 (K2 = 0: no second pair).
+// Generic bounds-checked fp32 GEMM product: C = A * B^T (+ A2 * B2^T),
+// A logically M x K, B logically N x K, A2 M x K2, B2 N x K2 (K2 = 0: no
+// second pair).
 enum GemmEpi : int32_t {
   EPI_STORE = 0,     // C[i][j] = acc
   EPI_GRAM_E = 1,    // C[i][j] = delta_ij - acc  (and C[j][i] if mirror)
@@ -254,8 +254,10 @@ struct GemmItem {
   int32_t M, N, K, K2;
   int32_t ti, tj;
   int32_t a_dtype, b_dtype;  // storage of A and A2, of B and B2
-  int32_t a_trans, b_trans;  // 0: row-major [M][K]; 1: stored [K][M]
-  int32_t a2_trans, b2_trans;
+  int32_t trans;             // GEMM_*_TRANS bits: stored [K][M], else row-major [M][K]
+  // GEMM_F16X2: the operands enter as 2^e times their values, e byte by byte
+  // (gemm_exps; further pairs as the first, both pairs with the same sum)
+  int32_t exps;
   int32_t epi;
   int32_t mirror;
   float beta;
@@ -264,13 +266,28 @@ struct GemmItem {
   int32_t pair_count;        //   [pair_base, pair_base + pair_count)
 };
 
-// One 64 x 64 output tile of a GemmItem's product (the item's own ti, tj are
-// not read on the device).  With a product's `mirror` set, its off-diagonal
-// tiles also write the transposed tile.
+// One square output tile (the list's edge) of a GemmItem's product (the
+// item's own ti, tj are not read on the device).  With a product's `mirror`
+// set, its off-diagonal tiles also write the transposed tile.
 struct GemmTile {
   int32_t item;
   int32_t ti, tj;
   int32_t pad;
+};
+
+// How a list's fp32 values enter the 16-bit matrix cores (gemm_f32.hip), and
+// how its operands are stored; a list's tiles are ordered by the latter.
+enum GemmSplit : int32_t { GEMM_BF16X3 = 0, GEMM_F16X2 = 1 };
+enum : int32_t { GEMM_A_TRANS = 1, GEMM_B_TRANS = 2, GEMM_A2_TRANS = 4, GEMM_B2_TRANS = 8 };
+inline int32_t gemm_exps(int a, int b, int a2 = 0, int b2 = 0) {
+  return (int32_t)((uint32_t)(a & 255) | (uint32_t)(b & 255) << 8 | (uint32_t)(a2 & 255) << 16 |
+                   (uint32_t)(b2 & 255) << 24);
+}
+enum GemmMode : int32_t { GEMM_ROWS = 0, GEMM_KMAJOR = 1, GEMM_ANY = 2 };
+struct GemmRun {
+  int32_t split;
+  int32_t tile;              // tile edge: 64 or 128
+  int32_t n[3];              // tiles of each GemmMode, in this order
 };
 
 // Compose (AOC) descriptors: one entry per (layer, group).
@@ -371,17 +388,20 @@ hipError_t launch_writeout(const TiledMat* mats, const TileItem* items, int n_it
                            int master_index, int out_dtype, hipStream_t s);
 hipError_t launch_bf16_tiles(int big, const TiledMat* mats, const TileItem* items, int n_items, float beta,
                              hipStream_t s, int vjp = 0, int step = 0);
-// The last n_km tiles must be of single-pair products with both operands
-// stored k-major; they run on the k-major instantiation.
-hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, int n_tiles, const char* name,
-                           hipStream_t s, int step = 0, const GemmPair* pairs = nullptr, int n_km = 0);
+hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const GemmRun& run, const char* name,
+                           hipStream_t s, int step = 0, const GemmPair* pairs = nullptr);
+// fp32 products: the largest |dL/d(output)| of every matrix into gmax (one
+// slot per matrix, zero before), from which the gradient iterate's
+// power-of-two scale is taken (nullptr: not scaled)
+hipError_t launch_vjp_grad_max(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype, float* gmax,
+                               hipStream_t s);
 hipError_t launch_vjp_load_grad(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype,
-                                hipStream_t s);
+                                const float* gmax, hipStream_t s);
 hipError_t launch_vjp_dot_partial(const TiledMat* mats, const TileItem* items, int n_items, int in_dtype,
                                   double* partials, hipStream_t s);
 hipError_t launch_vjp_dot_finish(const TiledMat* mats, int n_mats, const double* partials, hipStream_t s);
 hipError_t launch_vjp_writeout(const TiledMat* mats, const TileItem* items, int n_items, int in_dtype,
-                               int prescale, const int32_t* status, hipStream_t s);
+                               int prescale, const int32_t* status, const float* gmax, hipStream_t s);
 hipError_t launch_compose_init(const ComposeGroup* groups, int n_groups, int dtype, int64_t max_elems,
                                hipStream_t s);
 hipError_t launch_compose_combine(const ComposeGroup* groups, const CombineItem* items, int n_items,

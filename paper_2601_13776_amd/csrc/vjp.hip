@@ -1,5 +1,9 @@
 // Layout and pre-scaling kernels of the Björck vector-Jacobian product.
 //
+//   grad_max    : largest |dL/d(output)| of every matrix with fp32 products
+//                 (those products take the gradient iterate as half pieces:
+//                 it is scaled by the power of two that brings that value
+//                 to 1 to 2, and the result back)
 //   load_grad   : dL/d(output) from the caller's layout and dtype into the
 //                 tall, zero-padded fp32 gradient iterate (plus its bf16
 //                 copy for bf16 products)
@@ -42,11 +46,61 @@ __device__ inline void caller_tile(const TiledMat& d, const float* y, int R, int
   __syncthreads();
 }
 
+// Power-of-two exponent of matrix m's gradient scale (2^-e): that of its
+// largest value, 0 where nothing is scaled (bf16 products, no finite
+// non-zero value); clamped so that 2^-e and 2^e are normal numbers.
+__device__ inline int grad_exp(const TiledMat& d, const float* gmax, int m) {
+  if (!gmax || !d.gyt[0]) return 0;
+  const float v = gmax[m];
+  if (!(v > 0.f) || isinf(v)) return 0;
+  const int e = (int)(__float_as_uint(v) >> 23) - 127;
+  return e < -120 ? -120 : e > 120 ? 120 : e;
+}
+__device__ inline float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+
+// gmax[m] = max |dL/d(output)| (NaN ignored; a 64 x 64 tile of the caller's
+// layout per block).  One read of the gradient, HBM-bound.
+__global__ __launch_bounds__(256) void vjp_grad_max_kernel(const TiledMat* __restrict__ mats,
+                                                           const TileItem* __restrict__ items, int gout_dtype,
+                                                           float* __restrict__ gmax) {
+  __shared__ float red[4];
+  const TileItem it = items[blockIdx.x];
+  const TiledMat& d = mats[it.mat];
+  if (!d.gyt[0]) return;
+  const int R = it.ti * TB, C = it.tj * TB;
+  float m = 0.f;
+  if (R + TB <= d.rows && C + TB <= d.cols && vec8_ok(d.gout, d.ld_gout, gout_dtype)) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      float v[8];
+      load8_f32(d.gout, (int64_t)(R + (threadIdx.x >> 3) + 32 * h) * d.ld_gout + C + 8 * (threadIdx.x & 7),
+                gout_dtype, v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(v[i]));
+    }
+  } else {
+    for (int e = threadIdx.x; e < TB * TB; e += 256) {
+      const int r = R + e / TB, c = C + e % TB;
+      if (r < d.rows && c < d.cols) m = fmaxf(m, fabsf(load_as_f32(d.gout, (int64_t)r * d.ld_gout + c, gout_dtype)));
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    atomicMax(reinterpret_cast<unsigned int*>(gmax + it.mat), __float_as_uint(m));
+  }
+}
+
 __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __restrict__ mats,
-                                                            const TileItem* __restrict__ items, int gout_dtype) {
+                                                            const TileItem* __restrict__ items, int gout_dtype,
+                                                            const float* __restrict__ gmax) {
   __shared__ float tile[TB][TB + 1];
   const TileItem it = items[blockIdx.x];
   const TiledMat& d = mats[it.mat];
+  const float gs = pow2(-grad_exp(d, gmax, it.mat));
   const int R = it.ti * TB, C = it.tj * TB;  // tile origin in the tall padded layout
   float* y = d.gy[0];
   uint16_t* yc = static_cast<uint16_t*>(d.yc[0]);
@@ -69,12 +123,12 @@ __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __re
     const int a = e / TB, b = e % TB;
     if (!d.transposed) {
       const int r = R + a, c = C + b;
-      tile[a][b] = (r < d.M && c < d.N) ? load_as_f32(d.gout, (int64_t)r * d.ld_gout + c, gout_dtype) : 0.f;
+      tile[a][b] = (r < d.M && c < d.N) ? gs * load_as_f32(d.gout, (int64_t)r * d.ld_gout + c, gout_dtype) : 0.f;
     } else {
       // caller element (C + a, R + b) is tall element (R + b, C + a)
       const int orow = C + a, ocol = R + b;
       tile[b][a] =
-          (orow < d.N && ocol < d.M) ? load_as_f32(d.gout, (int64_t)orow * d.ld_gout + ocol, gout_dtype) : 0.f;
+          (orow < d.N && ocol < d.M) ? gs * load_as_f32(d.gout, (int64_t)orow * d.ld_gout + ocol, gout_dtype) : 0.f;
     }
   }
   __syncthreads();
@@ -150,7 +204,8 @@ __global__ __launch_bounds__(256) void vjp_dot_finish_kernel(const TiledMat* __r
 
 __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __restrict__ mats,
                                                            const TileItem* __restrict__ items, int in_dtype,
-                                                           int prescale, const int32_t* __restrict__ status) {
+                                                           int prescale, const int32_t* __restrict__ status,
+                                                           const float* __restrict__ gmax) {
   __shared__ float tile[TB][TB + 1];
   const TileItem it = items[blockIdx.x];
   const TiledMat& d = mats[it.mat];
@@ -158,6 +213,7 @@ __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __res
   const float* gy = d.gy[d.gy_final];
   const int st = status[d.status_index];
   const float inv = *d.inv_norm;
+  const float us = pow2(grad_exp(d, gmax, it.mat));   // undoes load_grad's scale
   const bool spec = prescale == ORTH_PRESCALE_SPECTRAL;
   const bool frob = prescale == ORTH_PRESCALE_FROBENIUS || spec;   // a term in W
   const float dscale = st != ORTH_MAT_OK ? 0.f : spec ? (float)d.sb[SB_DSCALE] : (float)(*d.dot) * inv;
@@ -189,6 +245,8 @@ __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __res
         }
         if (npair)
           for (int i = 0; i < 8; ++i) v[i] += rank1(r, c + i);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] *= us;
       }
       store8_f32(d.out, (int64_t)r * d.ld_out + c, in_dtype, v);
     }
@@ -208,8 +266,9 @@ __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __res
       const float w = load_as_f32(d.in, (int64_t)r * d.ld_in + c, in_dtype);
       v = inv * (tile[x][y] - dscale * w);
       if (npair) v += d.transposed ? rank1(c, r) : rank1(r, c);
+      v *= us;
     } else {
-      v = tile[x][y];
+      v = tile[x][y] * us;
     }
     store_from_f32(d.out, (int64_t)r * d.ld_out + c, in_dtype, v);
   }
@@ -217,11 +276,21 @@ __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __res
 
 }  // namespace
 
+hipError_t launch_vjp_grad_max(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype, float* gmax,
+                               hipStream_t s) {
+  if (n_items <= 0) return hipSuccess;
+  timing_begin("vjp_grad_max", s);
+  hipLaunchKernelGGL(vjp_grad_max_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax);
+  hipError_t e = hipGetLastError();
+  timing_end("vjp_grad_max", s);
+  return e;
+}
+
 hipError_t launch_vjp_load_grad(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype,
-                                hipStream_t s) {
+                                const float* gmax, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   timing_begin("vjp_load_grad", s);
-  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype);
+  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax);
   hipError_t e = hipGetLastError();
   timing_end("vjp_load_grad", s);
   return e;
@@ -247,10 +316,11 @@ hipError_t launch_vjp_dot_finish(const TiledMat* mats, int n_mats, const double*
 }
 
 hipError_t launch_vjp_writeout(const TiledMat* mats, const TileItem* items, int n_items, int in_dtype,
-                               int prescale, const int32_t* status, hipStream_t s) {
+                               int prescale, const int32_t* status, const float* gmax, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   timing_begin("vjp_writeout", s);
-  hipLaunchKernelGGL(vjp_writeout_kernel, dim3(n_items), dim3(256), 0, s, mats, items, in_dtype, prescale, status);
+  hipLaunchKernelGGL(vjp_writeout_kernel, dim3(n_items), dim3(256), 0, s, mats, items, in_dtype, prescale, status,
+                     gmax);
   hipError_t e = hipGetLastError();
   timing_end("vjp_writeout", s);
   return e;

@@ -310,14 +310,24 @@ hipError_t launch_bf16_tiles(int, const TiledMat*, const TileItem* items, int n,
   table(items, n, "launch_bf16_tiles");
   return launched();
 }
-hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, int n_tiles, const char* name, hipStream_t,
-                           int, const GemmPair*, int n_km) {
-  if (n_km < 0 || n_km > n_tiles) violation("k-major tile count out of range", name, 0, (size_t)n_km);
+hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const GemmRun& run, const char* name,
+                           hipStream_t, int, const GemmPair*) {
+  if (run.tile != 64 && run.tile != 128) violation("tile edge", name, 0, (size_t)run.tile);
+  for (int k : run.n)
+    if (k < 0) violation("tile count out of range", name, 0, (size_t)k);
+  if (run.split == GEMM_F16X2 && run.n[GEMM_KMAJOR] + run.n[GEMM_ANY] > 0)
+    violation("two pieces planned for other than row-major products", name, 0, 0);
+  const int n_tiles = run.n[0] + run.n[1] + run.n[2];
   if (n_tiles > 0) table(items, 1, name);
   table(tiles, n_tiles, name);
   return launched();
 }
-hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, hipStream_t) {
+hipError_t launch_vjp_grad_max(const TiledMat*, const TileItem* items, int n, int, float* gmax, hipStream_t) {
+  table(items, n, "launch_vjp_grad_max");
+  table(gmax, 1, "launch_vjp_grad_max (slots)");
+  return launched();
+}
+hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, const float*, hipStream_t) {
   table(items, n, "launch_vjp_load_grad");
   return launched();
 }
@@ -329,7 +339,8 @@ hipError_t launch_vjp_dot_finish(const TiledMat* mats, int n, const double*, hip
   table(mats, n, "launch_vjp_dot_finish");
   return launched();
 }
-hipError_t launch_vjp_writeout(const TiledMat*, const TileItem* items, int n, int, int, const int32_t*, hipStream_t) {
+hipError_t launch_vjp_writeout(const TiledMat*, const TileItem* items, int n, int, int, const int32_t*, const float*,
+                               hipStream_t) {
   table(items, n, "launch_vjp_writeout");
   return launched();
 }

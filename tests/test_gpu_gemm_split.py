@@ -1,0 +1,125 @@
+"""fp32 products on 16-bit matrix cores: the sizes where the tiles, the
+K-steps and the choice of tile edge can go wrong, the values that the split
+cannot carry (infinities, overflow), and the scaling of gradients."""
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import bjorck, bjorck_grad, checks
+from paper_2601_13776_amd import orth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = 1e-5   # fp32 products against the float64 oracle (measured: below 1e-6)
+
+
+def _rand(seed, *shape):
+    return np.random.default_rng(seed).standard_normal(shape).astype(np.float32)
+
+
+def _run(mats, iters, **kw):
+    ins = [torch.from_numpy(m).to(DEV) for m in mats]
+    outs = [torch.empty_like(t) for t in ins]
+    orth.orth_orthogonalize_batched(ins, outs, iters, **kw)
+    return [t.cpu().numpy().astype(np.float64) for t in outs]
+
+
+# 64-tiles: K of whole steps only, with a remainder, below one step; rows at
+# the edges of tiles
+@pytest.mark.parametrize("shape", [(129, 3), (129, 31), (160, 65), (64, 200), (191, 96), (257, 127), (128, 65)])
+def test_small_lists(shape):
+    m = _rand(1, *shape)
+    got = _run([m], 8)[0]
+    assert checks.relative_difference(got, bjorck.bjorck(m.astype(np.float64), 8)) <= TOL
+
+
+# enough 128-tiles for every compute unit: the 128-tile kernel, on shapes
+# that fill and that overhang its tiles
+@pytest.mark.parametrize("shape,n", [((512, 512), 16), ((500, 449), 16), ((130, 1030), 18), ((321, 640), 18)])
+@pytest.mark.parametrize("prescale", ["frobenius", "none"])
+def test_big_tile_lists(shape, n, prescale):
+    rng = np.random.default_rng(2)
+    mats = [(rng.standard_normal(shape) * (0.02 if prescale == "none" else 3.0)).astype(np.float32) for _ in range(n)]
+    got = _run(mats, 6, prescale=prescale)
+    for i in (0, n - 1):
+        ref = bjorck.bjorck(mats[i].astype(np.float64), 6, prescale=prescale)
+        assert checks.relative_difference(got[i], ref) <= TOL
+
+
+# light rows keep their own relative accuracy beside rows 2^10 times larger
+# (the half pieces' range)
+def test_row_scales():
+    m = _rand(3, 192, 128)
+    m[::7] *= 1024.0
+    got = _run([m], 5)[0]
+    ref = bjorck.bjorck(m.astype(np.float64), 5)
+    light = np.arange(192) % 7 != 0
+    assert checks.relative_difference(got[light], ref[light]) <= TOL
+
+
+# an infinity comes out as fp32 arithmetic has it, and a value that rounds to
+# a bfloat16 infinity keeps its fp32 result, on row-major and odd-sized
+# products
+@pytest.mark.parametrize("c,og", [(64, 64), (37, 29)])
+def test_nonfinite_products(c, og):
+    rko = _rand(4, 1, og, c)
+    rko[0, 3, 5] = np.inf
+    rko[0, 7] = 0.0
+    rko[0, 7, 2] = np.float32(3.399e38)
+    proj = (_rand(5, 1, 2, c, c // 2) / np.sqrt(2.0 * c)).astype(np.float32)
+    R, P = torch.from_numpy(rko).to(DEV), torch.from_numpy(proj).to(DEV)
+    K = torch.empty(og, c, 2, 2, device=DEV)
+    orth.orth_build_conv_kernels_batched([dict(geom=(c, og, 2, 1, 1, 1), rko=R, proj=P, kernel=K)])
+    got = K.cpu().numpy()
+
+    def compose(t, p):
+        y = t @ p[0]
+        h = [y, t - y]
+        return np.stack([np.stack([h[b] @ p[1] for b in range(2)]),
+                         np.stack([h[b] - h[b] @ p[1] for b in range(2)])]).transpose(2, 3, 0, 1)
+    with np.errstate(all="ignore"):
+        ref = compose(rko[0], [v @ v.T for v in proj[0]])
+        v64 = proj[0].astype(np.float64)
+        ref64 = compose(np.nan_to_num(rko[0].astype(np.float64), posinf=0.0), [v @ v.T for v in v64])
+    assert np.array_equal(np.isnan(got[3]), np.isnan(ref[3])) and not np.isfinite(got[3]).any()
+    for rows in ([o for o in range(og) if o not in (3, 7)], [7]):
+        assert np.isfinite(got[rows]).all()
+        scale = np.abs(ref64[rows]).max()
+        assert checks.relative_difference(got[rows] / scale, ref64[rows] / scale) <= TOL
+
+
+# gradients of any power-of-two scale give the same result times that scale,
+# bit for bit (the products scale them themselves)
+@pytest.mark.parametrize("exp", [-90, -23, 17, 60])
+def test_gradient_scale(exp):
+    mats = [_rand(6, 150, 97), _rand(7, 96, 256)]
+    ws = [torch.from_numpy(m).to(DEV) for m in mats]
+    grads = [torch.from_numpy(_rand(8 + i, *m.shape)).to(DEV) for i, m in enumerate(mats)]
+
+    def vjp(gs):
+        out = [torch.empty_like(w) for w in ws]
+        orth.orth_orthogonalize_vjp_batched(ws, gs, out, 5)
+        return out
+    one = vjp(grads)
+    other = vjp([g * 2.0 ** exp for g in grads])
+    for a, b, m, g in zip(one, other, mats, grads):
+        assert torch.equal(a * 2.0 ** exp, b)
+        ref = bjorck_grad.bjorck_vjp(m.astype(np.float64), g.cpu().numpy().astype(np.float64), 5)
+        assert checks.relative_difference(a.cpu().numpy().astype(np.float64), ref) <= TOL
+
+
+# a NaN or an infinity in one gradient leaves the other matrices alone
+def test_gradient_nonfinite():
+    mats = [_rand(9, 130, 70), _rand(10, 130, 70)]
+    ws = [torch.from_numpy(m).to(DEV) for m in mats]
+    grads = [torch.from_numpy(_rand(11 + i, 130, 70)).to(DEV) for i in range(2)]
+    ref = [torch.empty_like(w) for w in ws]
+    orth.orth_orthogonalize_vjp_batched(ws, grads, ref, 4)
+    for bad in (float("nan"), float("inf")):
+        g = [grads[0].clone(), grads[1]]
+        g[0][5, 6] = bad
+        out = [torch.empty_like(w) for w in ws]
+        orth.orth_orthogonalize_vjp_batched(ws, g, out, 4)
+        assert not torch.isfinite(out[0]).all()
+        assert torch.equal(out[1], ref[1])
