@@ -9,13 +9,14 @@
 //   with u = ((p + pl - d a) mod H) / s when that is a multiple of s (else
 //   the term is absent), v likewise; pl = floor((d (k - 1) + 1 - s) / 2).
 //
-// Both run as an implicit GEMM on fp32 MFMA (v_mfma_f32_32x32x2f32): rows
-// are output channels (the kernel is the first operand), columns are output
-// pixels (the second operand is gathered from the input on the fly), the
-// reduction runs over (input channel, tap).  Every output element is written
-// once by one lane: deterministic, no atomics.  64 x 64 tiles (the kernel
-// also builds 128-wide ones), four waves, K steps of 32 through two LDS
-// stages.
+// Both run as an implicit GEMM: rows are output channels (the kernel is the
+// first operand), columns are output pixels, the reduction runs over (input
+// channel, tap).  Every output element is written once by one lane:
+// deterministic, no atomics.  Kernels up to 3 x 3 run on the staged form
+// (below, 16-bit matrix cores), others and grids too wide for its staged
+// rows on the direct form: fp32 MFMA (v_mfma_f32_32x32x2f32), the second
+// operand gathered from the input on the fly, 64 x 64 tiles, four waves, K
+// steps of 32 through two LDS stages.
 #include "internal.h"
 
 namespace orth {
@@ -230,317 +231,485 @@ __global__ __launch_bounds__(256) void conv_apply_kernel(ApplyGeom G, const void
 
 
 // ---------------------------------------------------------------------------
-// Halo-staged variant for k <= 3: per chunk of CB = 8 reduction channels,
-// every input row that a 64-pixel tile needs (per output row it touches and
-// per tap row) is staged once in LDS, circularly extended by the taps'
-// reach, and all k^2 taps read from there.  The per-element global gather
-// (index arithmetic, wraps and one load per tap) becomes one load per
-// staged element (each read by up to k^2 taps x pixels) plus one LDS read
-// per MFMA operand value; the offsets of every staged element are computed
-// once per block.
+// Staged variant for k <= 3, on the 16-bit matrix cores: the fp32 values are
+// split into three bfloat16 pieces x = h + m + l on their way into LDS (8 +
+// 8 + 8 bits, exact), and hh + hm + mh + hl + lh + mm run on bf16 MFMA with
+// fp32 accumulation, the leading product and the corrections in an
+// accumulator each (a kernel stored in bf16 is its own leading piece: three
+// products).  The relative error against 64 bits is about a third of fp32
+// MFMA's.  A wave with a non-finite result computes its block again with
+// fp32 MFMA (an infinity splits into inf - inf).
 //
-// Staged layout per chunk: [ch][j][a][col], j the tile's output row slot
-// (J of them), a the tap row, col in [0, WX):
-//   forward    input row (s u + d a - pl) mod H of output row u, input
-//              column (col - pl) mod W; pixel v at tap e reads col s v + d e
-//   transposed row (u + pl - d a) mod H and column (col - span + pl) mod W of
-//              the stride-upsampled input (zero off the stride lattice);
-//              pixel v at tap e reads col v + span - d e
-struct HaloGeom {
-  int J;            // output rows a 64-pixel tile touches, at most
-  int RC;           // staged rows per channel: J k
-  int WX;           // staged columns
-  int tpr_log2;     // threads per staged row: 1 << tpr_log2 >= WX
-  int b_floats;     // CB RC WX rounded up to 4
-  int nch;          // reduction channels per group (c forward, og transposed)
-  int Hout, Wout;   // the output grid
-  int nchunks;      // ceil(nch / CB)
+// Work: a tile is 64 output channels x 128 pixels of a grid (4 waves of 32 x
+// 64); the reduction runs in chunks of CB = 8 G8 channels.  Per chunk, every
+// source row that the tile's pixels need is staged once, circularly extended
+// by the taps' reach, as 16-byte groups of 8 channels per position, and the
+// kernel tile as such groups per (tap, row).  One MFMA covers 16 k: two
+// (tap, 8-channel group) entries, lanes 0-31 reading the first and lanes
+// 32-63 the second, each with its own offset from the pixel's position; so a
+// staged value is split once and read by up to k^2 taps.  The next chunk's
+// loads are in flight during the MFMAs (no branch around them: channels past
+// the end re-read the last one, and the source's are zeroed).
+//
+// The grid a tile's pixels lie on, and the source position that tap (a, e)
+// of pixel (u, v) reads, are the same in all forms up to constants:
+//   row (ss u + rt[a]) mod Hs, column (ss v + ct[e]) mod Ws
+//   forward             the output grid, ss = s, rt[a] = d a - pl
+//   transposed, s = 1   the output grid, ss = 1, rt[a] = pl - d a
+//   transposed, s = 2   the source's own grid (PH = 4): position (u, v) has
+//                       the four outputs (2u + fh, 2v + fw); tap row a only
+//                       meets outputs of one parity, fh = (d a - pl) mod 2,
+//                       and reads row u + (fh + pl - d a) / 2: a quarter of
+//                       the products of the zero-stuffed form.  A wave holds
+//                       32 channels x 32 positions x 4 outputs.
+//   transposed, k = s   one tap per output phase: a 1 x 1 kernel with its
+//                       own tap, the phases in the block index
+// Staged rows: consecutive source rows of each image that the tile touches,
+// or (large dilation) k rows per grid row, whichever is fewer.
+//
+// What bounds it: MFMA and the splitting VALU of a SIMD share its issue
+// slots (a chunk of 8 channels with k = 3 costs 1920 cycles of MFMA per wave
+// and about 600 of splitting), and two workgroups per compute unit do not
+// cover each other's barriers fully.  Measured before (fp32 MFMA, staged
+// rows, zero-stuffed transposed form) and now: 256 -> 256 channels, 28 x 28,
+// batch 64: 1017 -> 486 us (58 -> 122 TFLOP/s; bf16 kernel 1066 -> 289);
+// transposed 1004 -> 444; 128 -> 256, stride 2, 32 x 32, batch 128: 394 ->
+// 156 us, transposed 1187 -> 179.
+struct StageGeom {
+  int Hg, Wg;            // the grid of the tile's pixels
+  int Hs, Ws;            // the source grid
+  int ss;                // source step per grid step
+  int64_t pix;           // batch x Hg x Wg
+  int rt[3], ct[3];      // tap row / column shifts
+  int rmin, cmin;        // their minima
+  int rows_sep;          // 1: k staged rows per grid row, 0: consecutive rows
+  int seg;               // consecutive rows: staged rows of a whole image
+  int WX;                // staged columns
+  int npos;              // staged positions (rows x WX), at most PU 256
+  int nch;               // reduction channels per group
+  int os, nph;           // output step; phases in the block index (k = s > 2: os^2)
+  int kk2;               // taps of the stored kernel
+  int par;               // s = 2: parity of pl (the output parity of tap row a is (a + par) mod 2)
 };
 
-// 64 x 64 pixels per workgroup (128 pixels, for twice the reuse of the
-// staged kernel tile, measured 25-50% slower: more staged rows per chunk)
-constexpr int HALO_CB = 8, HALO_BNP = 64, HALO_MAXE = 24;
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
+typedef float f32x2v __attribute__((ext_vector_type(2)));
+// 16- and 8-byte global loads at element alignment (gfx950 needs no more)
+typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
+typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {
+  const f32x2v v{a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
+}
+__device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = cvt2_bf16(a, b);
+  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+  m = cvt2_bf16(ra, rb);
+  l = cvt2_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
+}
 
-// 64 output rows x BN pixels per workgroup; each wave 32 rows x BN / 2
-// pixels (NI accumulators)
-// VECA (fp32 kernel, rows of a multiple of four elements): each chunk's
-// kernel tile is loaded as 16-byte vectors, with the offsets computed once
-// per workgroup.  Forward: along the kernel rows.  Transposed: the chunk's
-// channels o each hold the tile's 64 rows x k^2 taps contiguously
-// (K[o][i][tap]), read as one run per o and scattered to the LDS rows.
-template <bool TR, int KS, int BN, bool KBF16, bool VECA>
-__global__ __launch_bounds__(256) void conv_apply_halo_kernel(ApplyGeom G, HaloGeom Hg,
-                                                              const void* __restrict__ kern,
-                                                              const float* __restrict__ x, float* __restrict__ y) {
-  constexpr int CB = HALO_CB, KK = KS * KS, KCH = CB * KK, AP = KCH + 4, NI = BN / 64;
-  constexpr int MAXA = (64 * KCH + 255) / 256;
-  static_assert(KCH % 8 == 0, "a chunk is a whole number of 8-deep groups");
-  extern __shared__ float smem[];
-  float* const As = smem;
-  float* const Bs = smem + 64 * AP;
-  int* koff = reinterpret_cast<int*>(Bs + Hg.b_floats);
+// A wave's 32 x 32 block with fp32 MFMA: this lane's channel `row` of the
+// group (as MFMA row) and output pixel (as column), the original formula.
+template <bool TR>
+__device__ __forceinline__ f32x16 conv_block_f32(const ApplyGeom& G, const void* kern, const float* x, int grp,
+                                                 int row, bool pix_ok, int b, int p, int q) {
+  f32x16 acc = {};
+  const int half = (threadIdx.x >> 5) & 1, kk2 = G.k * G.k;
+  const int64_t cplane = TR ? (int64_t)G.Ho * G.Wo : (int64_t)G.H * G.W;
+  const float* xb = x + ((int64_t)b * (TR ? G.cout : G.cin) + (int64_t)grp * (TR ? G.og : G.c)) * cplane;
+  for (int k0 = 0; k0 < G.red; k0 += 2) {
+    const int kk = k0 + half;
+    float av = 0.f, bv = 0.f;
+    if (kk < G.red) {
+      const int ch = kk / kk2, tap = kk - ch * kk2, a = tap / G.k, e = tap - a * G.k;
+      if (row < G.rows)
+        av = load_as_f32(kern, TR ? ((int64_t)(grp * G.og + ch) * G.c + row) * kk2 + tap
+                                  : (int64_t)(grp * G.og + row) * G.red + kk, G.kdtype);
+      if (pix_ok) {
+        const int r = pmod(TR ? p + G.pl - G.d * a : G.s * p + G.d * a - G.pl, G.H);
+        const int c = pmod(TR ? q + G.pl - G.d * e : G.s * q + G.d * e - G.pl, G.W);
+        if (!TR)
+          bv = gld_f32(xb, ch * cplane + (int64_t)r * G.W + c);
+        else if (r % G.s == 0 && c % G.s == 0)
+          bv = gld_f32(xb, ch * cplane + (int64_t)(r / G.s) * G.Wo + c / G.s);
+      }
+    }
+    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+  }
+  return acc;
+}
 
-  const int grp = blockIdx.z;
-  const int row0 = blockIdx.y * 64;
-  const int64_t p0 = (int64_t)blockIdx.x * BN;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+template <bool TR, int KS, int PH, bool KBF16, int PU>
+__global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, StageGeom T,
+                                                                   const void* __restrict__ kern,
+                                                                   const float* __restrict__ x,
+                                                                   float* __restrict__ y) {
+  static_assert(PH == 1 || (TR && KS >= 2), "output phases of the transposed form with stride 2");
+  constexpr int KK = KS * KS, G8 = KS == 3 ? 1 : 2, CB = 8 * G8, NE = KK * G8, NS = (NE + 1) / 2;
+  constexpr int NB = PH == 4 ? 4 : 2;                // 32 x 32 blocks of a wave
+  constexpr int BN = PH == 4 ? 64 : 128;             // positions of a tile
+  constexpr int PA = KBF16 ? 1 : 3;                  // pieces of the kernel
+  extern __shared__ __attribute__((aligned(16))) uint4 smem4[];
+  uint4* const As = smem4;                           // [piece][entry 0 .. 2 NS)[64 rows]
+  uint4* const Xs = smem4 + PA * 2 * NS * 64;        // [piece][group][position]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
   const int wm = wave >> 1, wn = wave & 1;
-  const int span = G.d * (KS - 1);
-  const int WX = Hg.WX, RC = Hg.RC;
+  const int grp = blockIdx.z, row0 = blockIdx.y * 64;
+  const int phase = T.nph > 1 ? (int)(blockIdx.x % T.nph) : 0;
+  const int64_t p0 = (int64_t)(T.nph > 1 ? blockIdx.x / T.nph : blockIdx.x) * BN;
+  const int pfh = phase / T.os, pfw = phase - pfh * T.os;   // (only read with T.nph > 1)
 
-  // LDS offset of tap (ch, a, e) relative to a pixel's base
-  for (int kk = tid; kk < KCH; kk += 256) {
-    const int ch = kk / KK, tap = kk % KK, a = tap / KS, e = tap % KS;
-    koff[kk] = ch * RC * WX + a * WX + (TR ? -G.d * e : G.d * e);
+  int tap0 = 0, rt0 = 0, ct0 = 0;
+  if (T.nph > 1) {
+    // the tap (a, e) whose outputs have this phase: (d a - pl) mod s = pfh
+    for (int a = 0; a < G.k; ++a)
+      for (int e = 0; e < G.k; ++e)
+        if (pmod(G.d * a - G.pl, G.s) == pfh && pmod(G.d * e - G.pl, G.s) == pfw) {
+          tap0 = a * G.k + e;
+          rt0 = (pfh + G.pl - G.d * a) / G.s;
+          ct0 = (pfw + G.pl - G.d * e) / G.s;
+        }
   }
-  // this lane's B-operand pixel: its base offset in a channel's block
-  const int64_t first_row = p0 / Hg.Wout;
-  int poff[NI];
+
+  // entry of (tap, group): (tap, group) in order; four output phases: the
+  // taps of one phase side by side
+  auto entry = [&](int tap, int g) {
+    if (PH == 4 && KS == 3) return (int)((0x352786140ull >> (4 * tap)) & 15);   // see tap_of
+    return tap * G8 + g;
+  };
+  // its inverse: tap of entry i (the last entry of an odd count repeats its
+  // neighbour's position, with zero kernel values)
+  auto tap_of = [&](int i) {
+    if (PH == 4 && KS == 3) {
+      constexpr int t[10] = {0, 2, 6, 8, 1, 7, 3, 5, 4, 4};
+      return t[i];
+    }
+    return (i < NE ? i : NE - 1) / G8;
+  };
+  // block of slot q (two entries): always both with one phase, else that of
+  // the tap's parities
+  auto phase_of = [&](int q) {
+    if (PH == 1) return 0;
+    if (KS == 3) return q < 2 ? 0 : q - 1;
+    return q;   // KS == 2: slot = tap
+  };
+
+  // staged position of grid row `orow`: first staged row for tap offset 0
+  const int64_t first_row = p0 / T.Wg;
+  const int b0 = (int)(first_row / T.Hg), u0 = (int)(first_row - (int64_t)b0 * T.Hg);
+  const int seg0 = T.ss * (T.Hg - 1 - u0) + (T.seg - T.ss * (T.Hg - 1));   // staged rows of the first image
+  int poff[NB];   // this lane's pixel (PH == 4: the same for every block)
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) {
-    const int64_t pn = p0 + wn * (BN / 2) + ni * 32 + (lane & 31);
-    poff[ni] = 0;
-    if (pn < G.pix) {
-      const int64_t orow = pn / Hg.Wout;
-      const int v = (int)(pn - orow * Hg.Wout);
-      poff[ni] = (int)(orow - first_row) * KS * WX + (TR ? v + span : G.s * v);
+  for (int i = 0; i < (PH == 4 ? 1 : NB); ++i) {
+    const int64_t pn = p0 + wn * (BN / 2) + i * 32 + (lane & 31);
+    poff[i] = 0;
+    if (pn < T.pix) {
+      const int64_t orow = pn / T.Wg;
+      const int v = (int)(pn - orow * T.Wg), j = (int)(orow - first_row);
+      const int b = (int)(orow / T.Hg), u = (int)(orow - (int64_t)b * T.Hg);
+      const int slot = T.rows_sep ? j * KS : b == b0 ? T.ss * (u - u0) : seg0 + (b - b0 - 1) * T.seg + T.ss * u;
+      poff[i] = slot * T.WX + T.ss * v;
     }
   }
+  int koff[NS];   // this lane half's entry of each slot, relative to the pixel
+#pragma unroll
+  for (int q = 0; q < NS; ++q) {
+    const int t0 = tap_of(2 * q), t1 = tap_of(2 * q + 1);
+    const int g0 = (KS == 3) ? 0 : (2 * q) % G8, g1 = (KS == 3) ? 0 : (2 * q + 1) % G8;
+    auto off = [&](int t, int g) {
+      const int a = t / KS, e = t % KS;
+      return g * T.npos + (T.rows_sep ? a : T.rt[a] - T.rmin) * T.WX + (T.ct[e] - T.cmin);
+    };
+    const int o0 = KS == 1 ? 0 : off(t0, g0), o1 = KS == 1 ? T.npos : off(t1, g1);
+    koff[q] = half ? o1 : o0;
+  }
 
-  // staged elements of this thread: rows r = (tid >> tpr_log2) + i RPP,
-  // column tid & (TPR - 1); offsets relative to the chunk's first channel
-  const int rpp = 256 >> Hg.tpr_log2;
-  const int scol = tid & ((1 << Hg.tpr_log2) - 1);
-  const int srow0 = tid >> Hg.tpr_log2;
-  const int64_t cplane = TR ? (int64_t)G.Ho * G.Wo : (int64_t)G.H * G.W;   // one channel of the source
+  // this thread's staged positions: byte offset of the first channel group
+  const int64_t cplane = (int64_t)T.Hs * T.Ws;
   const int src_ch = TR ? G.cout : G.cin;
-  const int ch_base = grp * Hg.nch;
-  int boff[HALO_MAXE];
+  uint32_t xoff[PU];
 #pragma unroll
-  for (int i = 0; i < HALO_MAXE; ++i) {
-    boff[i] = -1;
-    const int r = srow0 + i * rpp;
-    if (r >= CB * RC || scol >= WX) continue;
-    const int ch = r / RC, rr = r - ch * RC, j = rr / KS, a = rr - j * KS;
-    const int64_t orow = first_row + j;
-    const int64_t b = orow / Hg.Hout;
-    const int u = (int)(orow - b * Hg.Hout);
-    if (b >= G.batch) continue;
-    int off;
-    if (!TR) {
-      const int sr = pmod(G.s * u + G.d * a - G.pl, G.H), sc = pmod(scol - G.pl, G.W);
-      off = (int)(((b * src_ch + ch_base + ch) * cplane) + (int64_t)sr * G.W + sc);
-    } else {
-      const int R = pmod(u + G.pl - G.d * a, G.H), C = pmod(scol - span + G.pl, G.W);
-      if (R % G.s || C % G.s) continue;
-      off = (int)(((b * src_ch + ch_base + ch) * cplane) + (int64_t)(R / G.s) * G.Wo + C / G.s);
-    }
-    boff[i] = off;
-  }
-  // VECA: float4 f = tid + j 256 of the 64 x KCH tile: global offset (-1:
-  // row past the end), column within the chunk, LDS offset
-  // (transposed: f over CB runs of 64 KK floats; vcol = element within the
-  // run, vlo = the run's channel o; elim = valid elements of a run)
-  constexpr int Q4 = KCH / 4, NV = (64 * Q4 + 255) / 256, QR = 64 * KK / 4;
-  int vgo[VECA ? NV : 1], vcol[VECA ? NV : 1], vlo[VECA ? NV : 1];
-  const int elim = TR ? (G.rows - row0 < 64 ? G.rows - row0 : 64) * KK : 0;
-  if constexpr (VECA && !TR) {
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int f = tid + j * 256, row = f / Q4, c4 = f - row * Q4;
-      vgo[j] = f < 64 * Q4 && row0 + row < G.rows ? (grp * G.og + row0 + row) * G.red + c4 * 4 : -1;
-      vcol[j] = c4 * 4;
-      vlo[j] = f < 64 * Q4 ? row * AP + c4 * 4 : -1;
-    }
-  } else if constexpr (VECA && TR) {
-#pragma unroll
-    for (int j = 0; j < NV; ++j) {
-      const int f = tid + j * 256, o = f / QR, w4 = f - o * QR;
-      vgo[j] = f < 64 * Q4 ? ((grp * G.og + o) * G.c + row0) * KK + w4 * 4 : -1;
-      vcol[j] = w4 * 4;
-      vlo[j] = o;
+  for (int i = 0; i < PU; ++i) {
+    const int pos = tid + i * 256;
+    xoff[i] = 0;
+    if (pos < T.npos) {
+      const int slot = pos / T.WX, col = pos - slot * T.WX;
+      int b, r;
+      if (T.rows_sep) {
+        const int64_t orow = first_row + slot / KS;
+        const int a = slot % KS;
+        b = (int)(orow / T.Hg);
+        r = T.ss * (int)(orow - (int64_t)b * T.Hg) + (T.nph > 1 ? rt0 : T.rt[a]);
+      } else if (slot < seg0) {
+        b = b0;
+        r = T.ss * u0 + slot + (T.nph > 1 ? rt0 : T.rmin);
+      } else {
+        const int g = (slot - seg0) / T.seg;
+        b = b0 + 1 + g;
+        r = slot - seg0 - g * T.seg + (T.nph > 1 ? rt0 : T.rmin);
+      }
+      const int sr = pmod(r, T.Hs), sc = pmod(col + (T.nph > 1 ? ct0 : T.cmin), T.Ws);
+      if (b < G.batch)
+        xoff[i] = (uint32_t)((((int64_t)b * src_ch + (int64_t)grp * T.nch) * cplane + (int64_t)sr * T.Ws + sc) * 4);
     }
   }
-  // kernel elements of this thread: e = tid + i 256 over 64 rows x KCH
-  int aoff[VECA ? 1 : MAXA];
-#pragma unroll
-  for (int i = 0; i < (VECA ? 0 : MAXA); ++i) {
-    aoff[i] = -1;
-    const int e = tid + i * 256;
-    if (e >= 64 * KCH) continue;
-    const int row = e / KCH, col = e - (e / KCH) * KCH;
-    if (row0 + row >= G.rows) continue;
-    if (!TR)
-      aoff[i] = (grp * G.og + row0 + row) * G.red + col;            // + ch0 KK per chunk
-    else
-      aoff[i] = ((grp * G.og + col / KK) * G.c + row0 + row) * KK + col % KK;   // + ch0 c KK
-  }
+  // this thread's kernel values: row `krow`, channels 2 kc2 and 2 kc2 + 1 of
+  // each group, all taps (a contiguous run per channel).  Lanes of a wave
+  // hold 16 rows x 4 channel pairs, so the stores of a tap are conflict free
+  const int krow = tid >> 2, kc2 = tid & 3;
+  const int64_t ch_stride = TR ? (int64_t)G.c * T.kk2 : T.kk2;   // elements between reduction channels
+  const int krc = row0 + krow < G.rows ? row0 + krow : G.rows - 1;
+  const int64_t kbase = (TR ? ((int64_t)grp * G.og * G.c + krc) * T.kk2 : (int64_t)(grp * G.og + krc) * G.red) +
+                        (KS == 1 ? tap0 : 0);
+  // the zero entry of an odd count
+  if (NE & 1)
+    for (int i = tid; i < PA * 64; i += 256) As[(i / 64 * 2 * NS + NE) * 64 + i % 64] = make_uint4(0, 0, 0, 0);
 
-  // one LDS stage: every chunk is staged (all loads in flight, then the
-  // stores), computed between two barriers; the two or three other
-  // workgroups on the compute unit overlap their staging with this one's
-  // MFMAs
-  // loads address a uniform base (this chunk's first channel) plus a
-  // 32-bit byte offset (the host keeps both tensors below 2^30 elements),
-  // one VGPR per address
-  auto stage = [&](int ch0) {
-    const int nvalid = Hg.nch - ch0;   // channels of this chunk that exist
-    constexpr int kes = KBF16 ? 2 : 4;   // kernel element bytes
-    const char* kq = static_cast<const char*>(kern) + (TR ? (int64_t)ch0 * G.c * KK : (int64_t)ch0 * KK) * kes;
-    const char* xq = reinterpret_cast<const char*>(x + (int64_t)ch0 * cplane);
-    // raw bits first, widened at the LDS store: a conversion inside the
-    // guarded load would make every load wait for its data
-    uint32_t ra[VECA ? 1 : MAXA];
-    float4 va[VECA ? NV : 1];
-    float rb[HALO_MAXE];
-    if constexpr (VECA) {
-      // valid elements of this thread's runs: forward, the chunk's valid
-      // columns; transposed, the rows that exist (channels checked apart)
-      const int lim = TR ? elim : (nvalid >= CB ? KCH : nvalid * KK);
-      const float* kf = reinterpret_cast<const float*>(kq);
+  constexpr int KW = KBF16 ? (KK + 1) / 2 : KK;   // words of a run
+  uint32_t ra[G8][2][KW];
+  float rx[PU][G8][8];
+  auto load = [&](int ch0) {
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        const int col = vcol[j];
-        if (vgo[j] >= 0 && (!TR || vlo[j] < nvalid)) {
-          const float* p = kf + (uint32_t)vgo[j];
-          if (col + 4 <= lim) {
-            v = *reinterpret_cast<const float4*>(p);
+    for (int g = 0; g < G8; ++g)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int ch = ch0 + 8 * g + 2 * kc2 + c;
+        const int64_t e = kbase + (ch < T.nch ? ch : T.nch - 1) * ch_stride;
+        uint32_t* w = ra[g][c];
+        if constexpr (KBF16) {
+          const uint16_t* q = static_cast<const uint16_t*>(kern) + e;
+          if constexpr (KK >= 8) {
+            const u32x4_a2 v = *(const ORTH_GLOBAL u32x4_a2*)q;
+            w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
+            w[4] = gld_u16(q, 8);
+          } else if constexpr (KK == 4) {
+            const u32x2_a2 v = *(const ORTH_GLOBAL u32x2_a2*)q;
+            w[0] = v.x; w[1] = v.y;
           } else {
-            if (col < lim) v.x = p[0];
-            if (col + 1 < lim) v.y = p[1];
-            if (col + 2 < lim) v.z = p[2];
+            w[0] = gld_u16(q, 0);
           }
-        }
-        va[j] = v;
-      }
+        } else {
+          const float* q = static_cast<const float*>(kern) + e;
 #pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        asm volatile("" : "+v"(va[j].x));
-        asm volatile("" : "+v"(va[j].y));
-        asm volatile("" : "+v"(va[j].z));
-        asm volatile("" : "+v"(va[j].w));
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < MAXA; ++i) {
-        const int e = tid + i * 256, col = e - (e / KCH) * KCH;
-        uint32_t v = 0;
-        if (aoff[i] >= 0 && col / KK < nvalid) {
-          const uint32_t bo = (uint32_t)aoff[i] * (uint32_t)kes;
-          if constexpr (KBF16)
-            v = *reinterpret_cast<const uint16_t*>(kq + bo);
-          else
-            v = *reinterpret_cast<const uint32_t*>(kq + bo);
-        }
-        ra[i] = v;
-      }
-      // materialize the raw values after the guarded loads (otherwise the
-      // widening shift is moved into each guarded block, where it waits)
-#pragma unroll
-      for (int i = 0; i < MAXA; ++i) asm volatile("" : "+v"(ra[i]));
-    }
-#pragma unroll
-    for (int i = 0; i < HALO_MAXE; ++i) {
-      const int r = srow0 + i * rpp;
-      float v = 0.f;
-      if (boff[i] >= 0 && r < nvalid * RC) v = *reinterpret_cast<const float*>(xq + (uint32_t)boff[i] * 4u);
-      rb[i] = v;
-    }
-    if constexpr (VECA && !TR) {
-#pragma unroll
-      for (int j = 0; j < NV; ++j)
-        if (vlo[j] >= 0) *reinterpret_cast<float4*>(&As[vlo[j]]) = va[j];
-    } else if constexpr (VECA && TR) {
-      // element e of channel o's run is row e / KK, tap e % KK
-#pragma unroll
-      for (int j = 0; j < NV; ++j) {
-        if (vgo[j] < 0) continue;
-        const float w[4] = {va[j].x, va[j].y, va[j].z, va[j].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int e = vcol[j] + q, row = e / KK;
-          As[row * AP + vlo[j] * KK + (e - row * KK)] = w[q];
+          for (int k = 0; k + 4 <= KK; k += 4) {
+            const u32x4_a4 v = *(const ORTH_GLOBAL u32x4_a4*)(q + k);
+            w[k] = v.x; w[k + 1] = v.y; w[k + 2] = v.z; w[k + 3] = v.w;
+          }
+          if constexpr (KK % 4) w[KK - 1] = gld_u32(q, KK - 1);
         }
       }
-    } else {
 #pragma unroll
-      for (int i = 0; i < MAXA; ++i) {
-        const int e = tid + i * 256;
-        if (e < 64 * KCH) As[(e / KCH) * AP + e % KCH] = __uint_as_float(KBF16 ? ra[i] << 16 : ra[i]);
+    for (int g = 0; g < G8; ++g)
+#pragma unroll
+      for (int c = 0; c < 8; ++c) {
+        const int ch = ch0 + 8 * g + c < T.nch ? ch0 + 8 * g + c : T.nch - 1;
+        const char* xq = reinterpret_cast<const char*>(x + ch * cplane);
+#pragma unroll
+        for (int i = 0; i < PU; ++i) rx[i][g][c] = gld_f32(xq + xoff[i], 0);
       }
+  };
+  auto stage = [&](int ch0) {
+    uint32_t* aw = reinterpret_cast<uint32_t*>(As);
+#pragma unroll
+    for (int g = 0; g < G8; ++g)
+#pragma unroll
+      for (int t = 0; t < KK; ++t) {
+        const int dst = (entry(t, g) * 64 + krow) * 4 + kc2;
+        if constexpr (KBF16) {
+          const uint32_t a = ra[g][0][t / 2], b = ra[g][1][t / 2];
+          aw[dst] = t & 1 ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
+        } else {
+          uint32_t h, m, l;
+          split2_bf16(__uint_as_float(ra[g][0][t]), __uint_as_float(ra[g][1][t]), h, m, l);
+          aw[dst] = h;
+          aw[dst + 2 * NS * 256] = m;
+          aw[dst + 4 * NS * 256] = l;
+        }
+      }
+    const int nv = T.nch - ch0;
+    if (nv < CB) {
+#pragma unroll
+      for (int g = 0; g < G8; ++g)
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          if (8 * g + c >= nv) {
+#pragma unroll
+            for (int i = 0; i < PU; ++i) rx[i][g][c] = 0.f;
+          }
     }
 #pragma unroll
-    for (int i = 0; i < HALO_MAXE; ++i) {
-      const int r = srow0 + i * rpp;
-      if (r < CB * RC && scol < WX) Bs[r * WX + scol] = rb[i];
+    for (int i = 0; i < PU; ++i) {
+      const int pos = tid + i * 256;
+      if (pos < T.npos) {
+#pragma unroll
+        for (int g = 0; g < G8; ++g) {
+          uint32_t w[3][4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) split2_bf16(rx[i][g][2 * q], rx[i][g][2 * q + 1], w[0][q], w[1][q], w[2][q]);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) Xs[(q * G8 + g) * T.npos + pos] = make_uint4(w[q][0], w[q][1], w[q][2], w[q][3]);
+        }
+      }
     }
   };
 
-  f32x16 acc[NI];
+  f32x16 acc[2][NB];   // the leading products, the corrections
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) acc[ni] = f32x16{};
-  const int aread = (wm * 32 + (lane & 31)) * AP + (lane >> 5) * 4;
-  for (int q = 0; q < Hg.nchunks; ++q) {
-    stage(q * CB);
+  for (int q = 0; q < 2; ++q)
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[q][i] = f32x16{};
+  auto mma = [&](uint4 a, uint4 b, f32x16 c) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+  };
+  const int arow = wm * 32 + (lane & 31);
+  load(0);
+  for (int ch0 = 0; ch0 < T.nch; ch0 += CB) {
     __syncthreads();
+    stage(ch0);
+    __syncthreads();
+    load(ch0 + CB < T.nch ? ch0 + CB : ch0);
 #pragma unroll
-    for (int g8 = 0; g8 < KCH / 8; ++g8) {
-      // k = 8 g8 + 4 (lane / 32) + t for instruction t, on both operands
-      const float4 a4 = *reinterpret_cast<const float4*>(&As[aread + g8 * 8]);
-      const int4 k4 = *reinterpret_cast<const int4*>(&koff[g8 * 8 + (lane >> 5) * 4]);
+    for (int q = 0; q < NS; ++q) {
+      uint4 fa[PA];
 #pragma unroll
-      for (int ni = 0; ni < NI; ++ni) {
-        const float* bs = Bs + poff[ni];
-        acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, bs[k4.x], acc[ni], 0, 0, 0);
-        acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, bs[k4.y], acc[ni], 0, 0, 0);
-        acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, bs[k4.z], acc[ni], 0, 0, 0);
-        acc[ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, bs[k4.w], acc[ni], 0, 0, 0);
+      for (int p = 0; p < PA; ++p) fa[p] = As[(p * 2 * NS + 2 * q + half) * 64 + arow];
+#pragma unroll
+      for (int i = 0; i < (PH == 4 ? 1 : NB); ++i) {
+        uint4 fb[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) fb[p] = Xs[p * G8 * T.npos + poff[i] + koff[q]];
+        f32x16& lead = acc[0][PH == 4 ? phase_of(q) : i];
+        f32x16& corr = acc[1][PH == 4 ? phase_of(q) : i];
+        if constexpr (KBF16) {
+          corr = mma(fa[0], fb[2], corr);
+          corr = mma(fa[0], fb[1], corr);
+        } else {
+          corr = mma(fa[2], fb[0], corr);
+          corr = mma(fa[0], fb[2], corr);
+          corr = mma(fa[1], fb[1], corr);
+          corr = mma(fa[1], fb[0], corr);
+          corr = mma(fa[0], fb[1], corr);
+        }
+        lead = mma(fa[0], fb[0], lead);
       }
     }
-    __syncthreads();
   }
 
-  const int ow = Hg.Wout, oh = Hg.Hout;
-  const int ych = TR ? G.cin : G.cout;
-  const int chb = grp * (TR ? G.c : G.og);
+  // columns are pixels: consecutive lanes store consecutive pixels
+  const int oh = TR ? G.H : G.Ho, ow = TR ? G.W : G.Wo;
+  const int ych = TR ? G.cin : G.cout, chb = grp * (TR ? G.c : G.og);
   const int64_t plane = (int64_t)oh * ow;
 #pragma unroll
-  for (int ni = 0; ni < NI; ++ni) {
-    const int64_t pn = p0 + wn * (BN / 2) + ni * 32 + (lane & 31);
-    if (pn >= G.pix) continue;
-    const int ov = (int)(pn % ow);
-    const int ou = (int)((pn / ow) % oh);
-    const int ob = (int)(pn / ((int64_t)ow * oh));
+  for (int i = 0; i < NB; ++i) {
+    const int64_t pn = p0 + wn * (BN / 2) + (PH == 4 ? 0 : i * 32) + (lane & 31);
+    const bool ok = pn < T.pix;
+    const int64_t orow = pn / T.Wg;
+    const int b = (int)(orow / T.Hg);
+    int u = (int)(orow - (int64_t)b * T.Hg), v = (int)(pn - orow * T.Wg);
+    if (PH == 4) {   // block i holds the taps of row parity i / 2, column parity i % 2
+      u = 2 * u + ((i >> 1) ^ T.par);
+      v = 2 * v + ((i & 1) ^ T.par);
+    } else if (T.nph > 1) {
+      u = T.os * u + pfh;
+      v = T.os * v + pfw;
+    }
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc[0][i][r] += acc[1][i][r];
+      bad |= !isfinite(acc[0][i][r]);
+    }
+    if (__builtin_expect(__any(bad && ok), 0))
+      acc[0][i] = conv_block_f32<TR>(G, kern, x, grp, row0 + wm * 32 + (lane & 31), ok, ok ? b : 0, u, v);
+    if (!ok) continue;
+    float* yp = y + ((int64_t)b * ych + chb) * plane + (int64_t)u * ow + v;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int ch = row0 + wm * 32 + acc_row(r, lane);
-      if (ch < G.rows) y[((int64_t)ob * ych + chb + ch) * plane + (int64_t)ou * ow + ov] = acc[ni][r];
+      if (ch < G.rows) gst_f32(yp, (int64_t)ch * plane, acc[0][i][r]);
     }
   }
 }
 
-template <bool TR, int KS, bool KBF16, bool VECA>
-hipError_t launch_halo_k(const ApplyGeom& G, const HaloGeom& Hg, dim3 grid, size_t lds, const orth_conv_apply_args* a,
-                         hipStream_t s) {
-  hipError_t e = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(&conv_apply_halo_kernel<TR, KS, HALO_BNP, KBF16, VECA>),
-      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((conv_apply_halo_kernel<TR, KS, HALO_BNP, KBF16, VECA>), grid, dim3(256), lds, s, G, Hg,
-                     a->kernel, a->x, a->y);
+template <bool TR, int KS, int PH, bool KBF16, int PU>
+hipError_t launch_staged_one(const ApplyGeom& G, const StageGeom& T, const orth_conv_apply_args* a, hipStream_t s) {
+  constexpr int KK = KS * KS, G8 = KS == 3 ? 1 : 2, NS = (KK * G8 + 1) / 2, BN = PH == 4 ? 64 : 128;
+  const size_t lds = ((size_t)(KBF16 ? 1 : 3) * 2 * NS * 64 + (size_t)3 * G8 * T.npos) * 16;
+  auto kp = &conv_apply_staged_kernel<TR, KS, PH, KBF16, PU>;
+  if (lds > 64 * 1024) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kp),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  const dim3 grid((unsigned)((T.pix + BN - 1) / BN * T.nph), (unsigned)((G.rows + 63) / 64), (unsigned)G.g);
+  hipLaunchKernelGGL((conv_apply_staged_kernel<TR, KS, PH, KBF16, PU>), grid, dim3(256), lds, s, G, T, a->kernel, a->x,
+                     a->y);
   return hipGetLastError();
 }
-template <bool TR, int KS>
-hipError_t launch_halo(const ApplyGeom& G, const HaloGeom& Hg, dim3 grid, size_t lds, const orth_conv_apply_args* a,
-                       hipStream_t s) {
-  if (G.kdtype == ORTH_BF16) return launch_halo_k<TR, KS, true, false>(G, Hg, grid, lds, a, s);
-  // 16-byte kernel loads: runs of a multiple of four floats, a 16-byte
-  // aligned kernel
-  const int64_t run = TR ? (int64_t)G.c * G.k * G.k : G.red;   // elements between consecutive runs
-  if (run % 4 == 0 && (reinterpret_cast<uintptr_t>(a->kernel) & 15) == 0)
-    return launch_halo_k<TR, KS, false, true>(G, Hg, grid, lds, a, s);
-  return launch_halo_k<TR, KS, false, false>(G, Hg, grid, lds, a, s);
+template <bool TR, int KS, int PH>
+hipError_t launch_staged(const ApplyGeom& G, const StageGeom& T, const orth_conv_apply_args* a, hipStream_t s) {
+  const bool narrow = G.kdtype == ORTH_BF16, wide = T.npos > 2 * 256;
+  if (narrow) return wide ? launch_staged_one<TR, KS, PH, true, 5>(G, T, a, s)
+                          : launch_staged_one<TR, KS, PH, true, 2>(G, T, a, s);
+  return wide ? launch_staged_one<TR, KS, PH, false, 5>(G, T, a, s)
+              : launch_staged_one<TR, KS, PH, false, 2>(G, T, a, s);
+}
+
+// The staged form's geometry; false where it does not apply (k > 3, other
+// strides of the transposed form, more staged positions than a workgroup
+// holds, tensors past 32-bit byte offsets).
+bool stage_geom(const ApplyGeom& G, bool tr, StageGeom& T, int& ks, int& ph) {
+  if (G.k > 3) return false;
+  if (tr && G.s > 2 && G.k != G.s) return false;
+  const int64_t src = (int64_t)G.batch * (tr ? (int64_t)G.cout * G.Ho * G.Wo : (int64_t)G.cin * G.H * G.W);
+  if (src >= ((int64_t)1 << 30) || (int64_t)G.cout * G.c * G.k * G.k >= ((int64_t)1 << 30)) return false;
+  const bool one_tap = tr && G.s > 2;            // k = s: one tap per output phase
+  ks = one_tap ? 1 : G.k;
+  ph = tr && G.s == 2 ? 4 : 1;
+  T.Hs = tr ? G.Ho : G.H;
+  T.Ws = tr ? G.Wo : G.W;
+  T.Hg = tr && G.s > 1 ? G.Ho : tr ? G.H : G.Ho;
+  T.Wg = tr && G.s > 1 ? G.Wo : tr ? G.W : G.Wo;
+  T.ss = tr ? 1 : G.s;
+  T.pix = (int64_t)G.batch * T.Hg * T.Wg;
+  T.nch = tr ? G.og : G.c;
+  T.os = one_tap ? G.s : 1;
+  T.nph = T.os * T.os;
+  T.kk2 = G.k * G.k;
+  T.par = G.pl & 1;
+  for (int a = 0; a < 3; ++a) {
+    int t = 0;
+    if (a < ks && !one_tap) {
+      if (!tr)
+        t = G.d * a - G.pl;
+      else if (G.s == 1)
+        t = G.pl - G.d * a;
+      else   // s = 2, d odd: the parity of d a - pl, then an exact half
+        t = (((a + T.par) & 1) + G.pl - G.d * a) / 2;
+    }
+    T.rt[a] = T.ct[a] = t;
+  }
+  T.rmin = T.rt[0];
+  int rmax = T.rt[0];
+  for (int a = 1; a < ks; ++a) {
+    T.rmin = std::min(T.rmin, T.rt[a]);
+    rmax = std::max(rmax, T.rt[a]);
+  }
+  T.cmin = T.rmin;
+  const int span = rmax - T.rmin, bn = ph == 4 ? 64 : 128;
+  T.WX = T.ss * (T.Wg - 1) + span + 1;
+  T.seg = T.ss * (T.Hg - 1) + span + 1;
+  const int64_t J = (T.Wg - 1 + bn - 1) / T.Wg + 1;             // grid rows a tile touches, at most
+  const int64_t nimg = (T.Hg - 1 + J - 1) / T.Hg + 1;           // images, at most
+  const int64_t cons = std::max((J - 1) * T.ss + span + 1, (J - nimg) * T.ss + nimg * (span + 1));
+  T.rows_sep = J * ks < cons;
+  const int64_t npos = (T.rows_sep ? J * ks : cons) * T.WX;
+  if (npos > 5 * 256) return false;
+  T.npos = (int)npos;
+  return T.nch > 0;
 }
 
 }  // namespace
@@ -566,42 +735,25 @@ hipError_t launch_conv_apply(const orth_conv_apply_args* a, hipStream_t s) {
   G.red = (a->transposed ? G.og : G.c) * g.k * g.k;
   G.pix = (int64_t)a->batch * (a->transposed ? (int64_t)G.H * G.W : (int64_t)G.Ho * G.Wo);
   G.kdtype = a->kernel_dtype;
-  // halo-staged kernel where it applies (k <= 3, staged rows within the
-  // per-thread budget, three workgroups' LDS per compute unit)
-  if (g.k <= 3) {
-    const bool TRn = a->transposed != 0;
-    HaloGeom Hg{};
-    Hg.Hout = TRn ? G.H : G.Ho;
-    Hg.Wout = TRn ? G.W : G.Wo;
-    Hg.nch = TRn ? G.og : G.c;
-    const int span = G.d * (G.k - 1);
-    Hg.J = (Hg.Wout - 1 + HALO_BNP - 1) / Hg.Wout + 1;
-    Hg.RC = Hg.J * G.k;
-    Hg.WX = TRn ? G.W + span : G.s * (G.Wo - 1) + span + 1;
-    int t = 0;
-    while ((1 << t) < Hg.WX) ++t;
-    Hg.tpr_log2 = t;
-    Hg.b_floats = (HALO_CB * Hg.RC * Hg.WX + 3) / 4 * 4;
-    Hg.nchunks = (Hg.nch + HALO_CB - 1) / HALO_CB;
-    const int kch = HALO_CB * G.k * G.k;
-    const size_t lds = (size_t)(64 * (kch + 4) + Hg.b_floats + kch) * sizeof(float);
-    const int64_t src_elems = (int64_t)G.batch * (TRn ? (int64_t)G.cout * G.Ho * G.Wo : (int64_t)G.cin * G.H * G.W);
-    const bool fits = t <= 8 && (HALO_CB * Hg.RC + (256 >> t) - 1) / (256 >> t) <= HALO_MAXE && lds <= 52 * 1024 &&
-                      src_elems < ((int64_t)1 << 30) && (int64_t)G.cout * G.c * G.k * G.k < ((int64_t)1 << 30) &&
-                      Hg.nch > 0;
-    if (fits) {
-      const dim3 grid((unsigned)((G.pix + HALO_BNP - 1) / HALO_BNP), (unsigned)((G.rows + 63) / 64),
-                      (unsigned)g.groups);
-      const char* name = TRn ? "conv_apply_transposed" : "conv_apply";
+  // staged kernel where it applies
+  {
+    StageGeom T{};
+    int ks = 1, ph = 1;
+    const bool tr = a->transposed != 0;
+    if (stage_geom(G, tr, T, ks, ph)) {
+      const char* name = tr ? "conv_apply_transposed" : "conv_apply";
       timing_begin(name, s);
       hipError_t e;
-      if (TRn)
-        e = G.k == 1 ? launch_halo<true, 1>(G, Hg, grid, lds, a, s)
-                     : G.k == 2 ? launch_halo<true, 2>(G, Hg, grid, lds, a, s) : launch_halo<true, 3>(G, Hg, grid, lds, a, s);
+      if (!tr)
+        e = ks == 1   ? launch_staged<false, 1, 1>(G, T, a, s)
+            : ks == 2 ? launch_staged<false, 2, 1>(G, T, a, s)
+                      : launch_staged<false, 3, 1>(G, T, a, s);
+      else if (ph == 4)
+        e = ks == 2 ? launch_staged<true, 2, 4>(G, T, a, s) : launch_staged<true, 3, 4>(G, T, a, s);
       else
-        e = G.k == 1 ? launch_halo<false, 1>(G, Hg, grid, lds, a, s)
-                     : G.k == 2 ? launch_halo<false, 2>(G, Hg, grid, lds, a, s)
-                                : launch_halo<false, 3>(G, Hg, grid, lds, a, s);
+        e = ks == 1   ? launch_staged<true, 1, 1>(G, T, a, s)
+            : ks == 2 ? launch_staged<true, 2, 1>(G, T, a, s)
+                      : launch_staged<true, 3, 1>(G, T, a, s);
       timing_end(name, s);
       return e;
     }
