@@ -53,8 +53,15 @@ __global__ __launch_bounds__(256) void exp_init_kernel(const ExpItem* __restrict
     const float inv = *it.inv;
     for (int64_t e = blockIdx.x * 256 + threadIdx.x; e < cc; e += (int64_t)gridDim.x * 256) {
       const float ah = it.a[e] * inv;
-      it.p0[e] = ah;
       it.out[e] = (e / c == e % c ? 1.f : 0.f) + ah;
+    }
+    const int64_t runs = it.ld_p / 8;
+    for (int64_t u = blockIdx.x * 256 + threadIdx.x; u < c * runs; u += (int64_t)gridDim.x * 256) {
+      const int64_t i = u / runs, j = (u - i * runs) * 8;
+      float v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = j + k < c ? it.a[i * c + j + k] * inv : 0.f;
+      store_pieces8(it.p0 + i * it.ld_p + j, v, pow2f(kExpExp));
     }
     return;
   }

@@ -30,19 +30,27 @@
 // value past half's range) is computed again with fp32 MFMA, so infinities,
 // NaN and overflow come out as fp32 arithmetic has them.
 //
-// What bounds it: the splitting.  VALU and MFMA instructions of a SIMD's
-// waves share its issue slots (8 full-rate VALU instructions beside each
-// 32 x 32 x 16 MFMA take 100 cycles per two of them, 64 without), and per
-// 32-deep step a 64 x 64 tile spends about 270 cycles of VALU per wave
-// beside 192 of MFMA (two pieces); 128 x 128 tiles halve the splitting per
-// product.  Without the staging a step would take 0.49 instead of 0.72 us
-// (128 x 128, two pieces, a tile per compute unit) and 0.16 instead of
-// 0.50 us (64 x 64).  So lists with a 128-tile for every compute unit use
-// those, others 64.  Measured before (fp32 MFMA) and now: exponential map of
-// 4 x 2048^2, 676 -> 287 us per power (102 -> 239 TFLOP/s, two pieces); conv
-// exponential of 512 channels, 776 -> 456 us per power (86 -> 147, three
-// pieces); update of a 2048 x 1024 iterate 58 -> 31 us, of eight 512^2 ones
-// 36 -> 21 us (two pieces).
+// Operands that only products read (transposed iterates, E, S', the powers
+// of an exponential) are stored as half pieces by the launch that makes them
+// (GEMM_PRE_*; store_pieces8 has the layout, in the space of the fp32
+// values) and go to LDS as they are.
+//
+// What bounds it where operands are split on the way: the splitting.  VALU
+// and MFMA instructions of a SIMD's waves share its issue slots (8 full-rate
+// VALU instructions beside each 32 x 32 x 16 MFMA take 100 cycles per two of
+// them, 64 without), and per 32-deep step a 64 x 64 tile spends about 270
+// cycles of VALU per wave beside 192 of MFMA (two pieces, both operands);
+// 128 x 128 tiles halve the splitting per product.  So lists with a
+// 128-tile for every compute unit use those, others 64.  With stored pieces
+// it is the wait for loads issued a step ahead (0.62 us per 32-deep step of
+// 256 128-tiles, 0.49 without loads; the L2 gives 17 TB/s and more to a
+// plain reader, 13.5 here).  Measured with fp32 MFMA, splitting on the way,
+// and stored pieces: exponential map of 4 x 2048^2, 676, 287, 251 us per
+// power (102, 239, 274 TFLOP/s); update of a 2048 x 1024 iterate 58, 31,
+// 28.8 us, of eight 512^2 ones 36, 21, 20.4 us; Gram matrix of 2048 x 1024
+// 34 -> 26.7, of eight 512^2 18 -> 15.4 us (the last two columns).  Three
+// pieces, split on the way: conv exponential of 512 channels, 776 -> 456 us
+// per power (86 -> 147 TFLOP/s).
 //
 // K advances in steps of 32 through two LDS stages (see the pipeline below).
 #include "internal.h"
@@ -54,7 +62,6 @@ typedef float f32x2v __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2v __attribute__((ext_vector_type(2)));
 
 namespace {
 
@@ -98,20 +105,10 @@ struct Split<GEMM_F16X2> {
   static __device__ constexpr int pa(int q) { return q == 0 ? 1 : 0; }
   static __device__ constexpr int pb(int q) { return q == 1 ? 1 : 0; }
   static constexpr float CORR = 1.f / 2048.f;
-  // (the packed conversion is written out: left to itself the compiler
-  // folds each multiplication into a v_fma_mixlo_f16, which takes twice the
-  // cycles of the multiplication and half a packed conversion)
-  static __device__ __forceinline__ uint32_t cvt2(float a, float b) {
-    uint32_t h;
-    asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(h) : "v"(a), "v"(b));
-    return h;
-  }
   static __device__ __forceinline__ void split2(float a, float b, float s, uint32_t (&o)[P]) {
-    o[0] = cvt2(a * s, b * s);
-    const f16x2v h = __builtin_bit_cast(f16x2v, o[0]);
-    o[1] = cvt2(fmaf(a, s, -(float)h.x) * 2048.f, fmaf(b, s, -(float)h.y) * 2048.f);
+    split2_f16(a, b, s, o[0], o[1]);
   }
-  static __device__ __forceinline__ float scale(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
+  static __device__ __forceinline__ float scale(int e) { return pow2f(e); }
   static __device__ __forceinline__ f32x16 mma(uint4 a, uint4 b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
                                                   0);
@@ -171,8 +168,13 @@ __device__ __forceinline__ f32x16 block_f32(const GemmItem& g, const GemmPair* e
     for (int k0 = 0; k0 < v.K; k0 += 2) {
       const int k = k0 + (lane >> 5);
       float a = 0.f, b = 0.f;
-      if (i < g.M && k < v.K) a = load_as_f32(v.A, v.atr ? k * v.lda + i : i * v.lda + k, g.a_dtype);
-      if (j < g.N && k < v.K) b = load_as_f32(v.B, v.btr ? k * v.ldb + j : j * v.ldb + k, g.b_dtype);
+      const int e0 = pair == 1 ? 2 : 0;
+      if (i < g.M && k < v.K)
+        a = g.trans & GEMM_PRE_A ? load_piece(v.A + i * v.lda * 4, k, pow2f(-exp_of(g.exps, e0)))
+                                 : load_as_f32(v.A, v.atr ? k * v.lda + i : i * v.lda + k, g.a_dtype);
+      if (j < g.N && k < v.K)
+        b = g.trans & GEMM_PRE_B ? load_piece(v.B + j * v.ldb * 4, k, pow2f(-exp_of(g.exps, e0 + 1)))
+                                 : load_as_f32(v.B, v.btr ? k * v.ldb + j : j * v.ldb + k, g.b_dtype);
       acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
     }
   }
@@ -188,7 +190,10 @@ __device__ __forceinline__ f32x16 block_f32(const GemmItem& g, const GemmPair* e
 // loads (rows past the end re-read the last ones: their results are not
 // stored), and what is left of each pair's K follows, value by value;
 // GEMM_ANY loads every step that way, as vectors where it can.
-template <int SC, int BM, int MODE>
+// PRE: operands stored as half pieces (whole steps only: K a multiple of 32)
+// go to LDS as they are; the epilogue is then that of the lists which use
+// them (GEMM_PRE_RIGHT: updates, GEMM_PRE_BOTH: Gram, S' and series items).
+template <int SC, int BM, int MODE, int PRE = GEMM_PRE_NONE>
 __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const GemmItem* __restrict__ items,
                                                                            const GemmTile* __restrict__ tiles,
                                                                            int step,
@@ -213,7 +218,9 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
   // (one row per lane) and the row-major stores are conflict free
   auto swz = [](int r) { return ((r >> 1) & 3) ^ ((r >> 3) & 1); };
   auto plane = [&](int s, int o, int p) { return smem + ((s * 2 + o) * P + p) * (BM * CH); };
-  // this thread's values: row-major (row rr, k 8 rc ..), k-major (rows tr .. tr + 3, k tk, tk + 1)
+  // this thread's values: row-major (row rr, k 8 rc ..; whole cache lines per
+  // load, 4 k of two rows, were no faster), k-major (rows tr .. tr + 3, k tk
+  // and tk + 1)
   const int rr = tid / CH, rc = tid % CH;
   const int tr = (tid % (BM / 4)) * 4, tk = (tid / (BM / 4)) * 2;
   const int exps = SC == GEMM_F16X2 ? item.exps : 0;
@@ -291,6 +298,13 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
   };
   auto stage = [&](int set, int s, int o) {
     const uint4 a = raw[set][o][0], b = raw[set][o][1];
+    if (PRE == GEMM_PRE_BOTH || (PRE == GEMM_PRE_RIGHT && o == 1)) {
+      // (8 h, then 8 l)
+      const int dst = rr * CH + (rc ^ swz(rr));
+      plane(s, o, 0)[dst] = a;
+      plane(s, o, 1)[dst] = b;
+      return;
+    }
     const float x[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
                         __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
     split_store(x, scl[set][o], MODE == GEMM_KMAJOR, s, o);
@@ -402,6 +416,21 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
     stage(buf, buf, 0);
     mfmas(f1);
   };
+  // an update's old values, on their way during the products
+  float src_v[MI][NI][PRE == GEMM_PRE_RIGHT ? 16 : 1];
+  if constexpr (PRE == GEMM_PRE_RIGHT) {
+    const float* src = item.src + item.src_step * st;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int a = row0 + wm * (BM / WM) + i * 32 + acc_row(r, lane);
+          const int b = col0 + wn * (BM / WN) + j * 32 + (lane & 31);
+          src_v[i][j][r] = gld_f32(src, (int64_t)(a < M ? a : M - 1) * item.ld_src + (b < N ? b : N - 1));
+        }
+  }
   if constexpr (MODE != GEMM_ANY) {
     if (next()) {
       loaded = 1;
@@ -422,7 +451,7 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
     }
   }
   // what the pipeline left (every wave is past the pipeline)
-  {
+  if constexpr (PRE == GEMM_PRE_NONE) {
     int s = 0;
     for (int p = 0; p < npairs; ++p) {
       const PairView v = pair_view(item, extra, p, st);
@@ -459,7 +488,8 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
       const int r = row0 + wm * (BM / WM) + i * 32 + (lane & 31);
       if (r < M && item.K > 0) {
         const PairView v = pair_view(item, extra, 0, st);
-        const float a = load_as_f32(v.A, v.atr ? r : r * v.lda, item.a_dtype);
+        const float a = PRE == GEMM_PRE_BOTH ? load_piece(v.A + r * v.lda * 4, 0, 1.f)
+                                             : load_as_f32(v.A, v.atr ? r : r * v.lda, item.a_dtype);
         all_nan &= isnan(a);
       } else if (r < M) {
         all_nan = false;
@@ -474,6 +504,72 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
     }
   }
 
+  if constexpr (PRE != GEMM_PRE_NONE) {
+    // Results that later products read as pieces are written 8 values (32
+    // bytes) at a time from a 32 x 33 region of LDS per wave, which holds a
+    // block's rows in one orientation and then the other.
+    float* Tt = reinterpret_cast<float*>(smem) + wave * (32 * 33);
+    const float po = pow2f((int)((uint32_t)item.trans << 16) >> 24);
+    auto wave_sync = [&]() {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+    };
+    // the block's values, `t` of this lane's column, to rows [r0, r0 + 32)
+    // x columns [c0, c0 + 32) of dst (limits rl, cl; zero past czero)
+    auto put_pieces = [&](const float (&t)[16], bool flip, float* dst, int64_t ld, int r0, int c0, int rl, int cl,
+                          int czero) {
+      wave_sync();
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        Tt[flip ? (lane & 31) * 33 + acc_row(r, lane) : acc_row(r, lane) * 33 + (lane & 31)] = t[r];
+      wave_sync();
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        const int e = q * 64 + lane, r = e >> 2, c = (e & 3) * 8;
+        float v[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v[k] = c0 + c + k < czero ? Tt[r * 33 + c + k] : 0.f;
+        if (r0 + r < rl && c0 + c < cl) store_pieces8(dst + (int64_t)(r0 + r) * ld + c0 + c, v, po);
+      }
+    };
+#pragma unroll
+    for (int bi = 0; bi < MI; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NI; ++bj) {
+        const f32x16& v = acc[0][bi][bj];
+        const int ibase = row0 + wm * (BM / WM) + bi * 32, jbase = col0 + wn * (BM / WN) + bj * 32;
+        const int j = jbase + (lane & 31);
+        float* C = static_cast<float*>(item.C) + item.c_step * st;
+        const int64_t ldc = item.ldc;
+        float t[16];
+        if constexpr (PRE == GEMM_PRE_RIGHT) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int i = ibase + acc_row(r, lane);
+            t[r] = src_v[bi][bj][r] + item.beta * v[r];
+            if (i < M && j < N) gst_f32(C, (int64_t)i * ldc + j, t[r]);
+          }
+          if (item.dst2) put_pieces(t, true, item.dst2 + item.d2_step * st, item.ld2, jbase, ibase, N, M, M);
+        } else if (item.epi == EPI_SERIES) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int i = ibase + acc_row(r, lane);
+            t[r] = item.beta * v[r];
+            // each element belongs to one item of the launch
+            if (i < M && j < N)
+              gst_f32(item.dst2, (int64_t)i * item.ld2 + j, gld_f32(item.dst2, (int64_t)i * item.ld2 + j) + t[r]);
+          }
+          if (C) put_pieces(t, false, C, ldc, ibase, jbase, M, (int)ldc, N);
+        } else {   // EPI_GRAM_E, EPI_NEG
+          const float one = item.epi == EPI_GRAM_E ? 1.f : 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) t[r] = (ibase + acc_row(r, lane) == j ? one : 0.f) - v[r];
+          put_pieces(t, false, C, ldc, ibase, jbase, M, N, N);
+          if (mirror) put_pieces(t, true, C, ldc, jbase, ibase, N, M, M);
+        }
+      }
+    return;
+  }
   const int epi = item.epi;
   float dev = 0.f;
 #pragma unroll
@@ -599,7 +695,7 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
   }
 }
 
-template <int SC, int BM, int MODE>
+template <int SC, int BM, int MODE, int PRE = GEMM_PRE_NONE>
 hipError_t launch_one(const GemmItem* items, const GemmTile* tiles, int n, int step, const GemmPair* pairs,
                       hipStream_t s) {
   if (n <= 0) return hipSuccess;
@@ -607,11 +703,11 @@ hipError_t launch_one(const GemmItem* items, const GemmTile* tiles, int n, int s
   // default limit with three pieces and 128-tiles
   constexpr int lds = 2 * 2 * Split<SC>::P * BM * 32 * 2;
   if constexpr (lds > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<SC, BM, MODE>),
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f32_kernel<SC, BM, MODE, PRE>),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL((gemm_f32_kernel<SC, BM, MODE>), dim3(n), dim3(BM == 64 ? 256 : 512), lds, s, items, tiles, step,
+  hipLaunchKernelGGL((gemm_f32_kernel<SC, BM, MODE, PRE>), dim3(n), dim3(BM == 64 ? 256 : 512), lds, s, items, tiles, step,
                      pairs);
   return hipGetLastError();
 }
@@ -626,10 +722,16 @@ hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const G
   hipError_t e = hipSuccess;
   const GemmTile* t = tiles;
   if (run.split == GEMM_F16X2) {
-    // only row-major fp32 products are planned with two pieces
-    e = run.n[GEMM_ROWS] != n ? hipErrorInvalidValue
-        : run.tile == 128     ? launch_one<GEMM_F16X2, 128, GEMM_ROWS>(items, t, n, step, pairs, s)
-                              : launch_one<GEMM_F16X2, 64, GEMM_ROWS>(items, t, n, step, pairs, s);
+    // only row-major products are planned with two pieces
+    const bool big = run.tile == 128;
+    if (run.n[GEMM_ROWS] != n)
+      e = hipErrorInvalidValue;
+    else if (run.pre == GEMM_PRE_RIGHT)
+      e = big ? launch_one<GEMM_F16X2, 128, GEMM_ROWS, GEMM_PRE_RIGHT>(items, t, n, step, pairs, s)
+              : launch_one<GEMM_F16X2, 64, GEMM_ROWS, GEMM_PRE_RIGHT>(items, t, n, step, pairs, s);
+    else
+      e = big ? launch_one<GEMM_F16X2, 128, GEMM_ROWS, GEMM_PRE_BOTH>(items, t, n, step, pairs, s)
+              : launch_one<GEMM_F16X2, 64, GEMM_ROWS, GEMM_PRE_BOTH>(items, t, n, step, pairs, s);
   } else {
     const bool big = run.tile == 128;
     e = big ? launch_one<GEMM_BF16X3, 128, GEMM_ROWS>(items, t, run.n[GEMM_ROWS], step, pairs, s)

@@ -510,7 +510,7 @@ struct GemmList {
   std::vector<int32_t> pending;   // add_all products without tiles yet
   int64_t pending64 = 0;          // their count of 64-tiles
   GemmItem last{};   // items.back() with its tile and mirror fields cleared
-  GemmRun run{GEMM_BF16X3, 64, {0, 0, 0}};
+  GemmRun run{GEMM_BF16X3, 64, {0, 0, 0}, GEMM_PRE_NONE};
   // at most this many tiles (the count with 64-tiles)
   size_t size() const { return tiles.size() + (size_t)pending64; }
   void clear() {
@@ -522,8 +522,8 @@ struct GemmList {
   // how every operand of the product is stored
   static GemmMode mode(const GemmItem& it) {
     if (it.a_dtype != ORTH_F32 || it.b_dtype != ORTH_F32) return GEMM_ANY;
-    if (it.trans == 0) return GEMM_ROWS;   // further pairs are row-major too
-    if (it.trans == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
+    if ((it.trans & GEMM_ANY_TRANS) == 0) return GEMM_ROWS;   // further pairs are row-major too
+    if ((it.trans & GEMM_ANY_TRANS) == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
       return GEMM_KMAJOR;
     return GEMM_ANY;
   }
@@ -609,12 +609,16 @@ hipError_t launch_list(const unsigned char* ws, size_t off, const GemmList& g, c
                          reinterpret_cast<const GemmTile*>(ws + off + g.items_bytes()), g.run, name, s, step, pairs);
 }
 
-// Exponents of operands of known range (GEMM_F16X2).  Iterates are scaled
-// to at most 1 (Frobenius) or to a largest singular value below sqrt(3)
-// where the iteration converges (spectral), E and the exponential map's
-// Ahat likewise, so 2^14 times their values stay below half's 65504.
-// Without pre-scaling nothing is known, and three bfloat16 pieces are used.
-constexpr int kIterExp = 14;
+// Products of operands of known range (iterates scaled by Frobenius or
+// spectral pre-scaling, E, Ahat, scaled gradients) take two half pieces, and
+// what only products read (the transposed iterates, E, S', the powers) is
+// stored as pieces (stored once, loaded once per tile of a row or column, so
+// splitting at the store does 1/8 to 1/32 of the work at 512^2 to 2048^2).
+// Without pre-scaling nothing is known about the range: three bfloat16
+// pieces of fp32 buffers.
+inline GemmRun ranged_run(bool ranged, int64_t n128, GemmPre pre) {
+  return GemmRun{ranged ? GEMM_F16X2 : GEMM_BF16X3, gemm_tile_edge(n128), {0, 0, 0}, ranged ? pre : GEMM_PRE_NONE};
+}
 
 }  // namespace
 
@@ -648,6 +652,7 @@ struct OrthoPlan {
   size_t off_power[2] = {0, 0};
   size_t off_partials = 0, off_inv = 0, off_status = 0;
   size_t table_bytes = 0, total_bytes = 0;
+  bool pieces = false;  // fp32 products: transposed iterates and E stored as half pieces
   int n_out_iter = 0;   // tiled matrices whose output buffer holds the fp32 iterate
 };
 
@@ -848,9 +853,9 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
       g128 += tn * (tn + 1) / 2;
       u128 += tiles_of(q.Mp, 128) * tn;
     }
-  const GemmSplit split = two_pieces ? GEMM_F16X2 : GEMM_BF16X3;
-  P.f32_gram.run = GemmRun{split, gemm_tile_edge(g128), {0, 0, 0}};
-  P.f32_update[0].run = P.f32_update[1].run = GemmRun{split, gemm_tile_edge(u128), {0, 0, 0}};
+  P.f32_gram.run = ranged_run(two_pieces, g128, GEMM_PRE_BOTH);
+  P.f32_update[0].run = P.f32_update[1].run = ranged_run(two_pieces, u128, GEMM_PRE_RIGHT);
+  P.pieces = two_pieces;
 
   // per-matrix buffers and descriptors
   int part_base = 0;
@@ -955,7 +960,10 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
         gi.ti = g.ti;
         gi.tj = g.tj;
         gi.a_dtype = gi.b_dtype = ORTH_F32;
-        gi.exps = two_pieces ? gemm_exps(kIterExp, kIterExp) : 0;
+        if (two_pieces) {
+          gi.exps = gemm_exps(kIterExp, kIterExp);
+          gi.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kIterExp);
+        }
         gi.epi = EPI_GRAM_E;
         gi.mirror = g.ti != g.tj;
         P.f32_gram.push_back(gi);
@@ -979,7 +987,10 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
           gi.ti = u.ti;
           gi.tj = u.tj;
           gi.a_dtype = gi.b_dtype = ORTH_F32;
-          gi.exps = two_pieces ? gemm_exps(kIterExp, kIterExp) : 0;
+          if (two_pieces) {
+            gi.exps = gemm_exps(kIterExp, kIterExp);
+            gi.trans = GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kIterExp);
+          }
           gi.epi = EPI_UPDATE;
           gi.beta = o->beta;
           P.f32_update[par].push_back(gi);
@@ -1578,9 +1589,12 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
     const orth_mat& m = mats[i];
     const int C = m.rows;
     const int64_t cc = (int64_t)C * C;
-    float* a = fbuf(cc);
-    float* ahat = fbuf(cc);
-    float* pp[2] = {fbuf(cc), p > 2 ? fbuf(cc) : nullptr};
+    // powers as half pieces, rows padded to whole k-steps with zeros
+    const int Cp = (int)round_up(C, 32);
+    float* a = fbuf((int64_t)C * Cp);
+    float* ahat = fbuf((int64_t)C * Cp);
+    // (A is read only until Ahat is written)
+    float* pp[2] = {p > 2 ? fbuf((int64_t)C * Cp) : nullptr, a};
     float* acc = fbuf(cc);
     float* inv = reinterpret_cast<float*>(dev(P.off_inv)) + i;
     TiledMat t{};
@@ -1617,6 +1631,7 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
     e.a = a;
     e.out = acc;
     e.p0 = ahat;
+    e.ld_p = Cp;
     e.inv = inv;
     e.c = C;
     e.k = 1;
@@ -1628,20 +1643,21 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
       GemmItem g{};
       g.A = k == 2 ? ahat : pp[(k - 1) & 1];
       g.B = ahat;              // A^T = -A: C = P_{k-1} Ahat = -(P_{k-1} Ahat^T)
-      g.lda = g.ldb = C;
-      g.K = C;
+      g.lda = g.ldb = Cp;
+      g.K = Cp;
       g.M = g.N = C;
-      g.C = pp[k & 1];
-      g.ldc = C;
+      g.C = k < p ? pp[k & 1] : nullptr;   // (nothing reads the last power)
+      g.ldc = Cp;
       g.dst2 = acc;
       g.ld2 = C;
-      g.exps = gemm_exps(kIterExp, kIterExp);
+      g.exps = gemm_exps(kExpExp, kExpExp);
+      g.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kExpExp);
       g.beta = -1.f / k;
       g.epi = EPI_SERIES;
       gemm_tiles(g, P.steps[k - 2]);
     }
   }
-  for (auto& g : P.steps) g.run.split = GEMM_F16X2;   // |Ahat| is about 1
+  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);   // |Ahat| is about 1
   P.total_bytes = align_up(A.off);
 }
 
@@ -1774,6 +1790,7 @@ struct VjpPlan {
   // fp32 products: a slot per matrix for the largest upstream gradient, zero
   // when the call starts
   bool f32 = false;
+  bool pieces = false;   // fp32 products: transposed iterates, E and S' stored as half pieces
   std::vector<float> gmax;
   size_t off_gmax = 0;
   size_t table_bytes = 0, total_bytes = 0;
@@ -1967,9 +1984,11 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
       g128 += tn * (tn + 1) / 2;
       u128 += tiles_of(P.mats[i].Mp, 128) * tn;
     }
-  const GemmSplit split = two_pieces ? GEMM_F16X2 : GEMM_BF16X3;
-  P.f_gram.run = P.b_s[0].run = P.b_s[1].run = GemmRun{split, gemm_tile_edge(g128), {0, 0, 0}};
-  P.f_upd.run = P.b_upd[0].run = P.b_upd[1].run = GemmRun{split, gemm_tile_edge(u128), {0, 0, 0}};
+  P.f_gram.run = P.b_s[0].run = P.b_s[1].run = ranged_run(two_pieces, g128, GEMM_PRE_BOTH);
+  P.f_upd.run = P.b_upd[0].run = P.b_upd[1].run = ranged_run(two_pieces, u128, GEMM_PRE_RIGHT);
+  P.pieces = two_pieces;
+  const int32_t pre_both = two_pieces ? GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT : 0;
+  const int32_t pre_right = two_pieces ? GEMM_PRE_B | GEMM_PRE_OUT : 0;
   P.f32 = n_fu > 0;
 
   Arena A;
@@ -2102,6 +2121,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
         g.exps = gemm_exps(x_exp, x_exp);
+        g.trans = pre_both | gemm_out_exp(x_exp);
         g.epi = EPI_GRAM_E;
         g.mirror = a != b;
         P.f_gram.push_back(g);
@@ -2126,6 +2146,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
           h.exps = gemm_exps(x_exp, 0, 0, x_exp);
+          h.trans = pre_both;
           h.epi = EPI_NEG;
           h.mirror = a != b;
           P.b_s[par].push_back(h);
@@ -2156,6 +2177,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
         g.exps = gemm_exps(x_exp, x_exp);
+        g.trans = pre_right | gemm_out_exp(x_exp);
         g.epi = EPI_UPDATE;
         g.beta = o->beta;
         P.f_upd.push_back(g);
@@ -2187,6 +2209,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
           h.exps = gemm_exps(0, x_exp, x_exp, 0);
+          h.trans = pre_right;
           h.epi = EPI_UPDATE;
           h.beta = o->beta;
           P.b_upd[par].push_back(h);
@@ -2282,7 +2305,7 @@ int ortho_enqueue(const orth_mat* mats, int32_t n, const orth_bjorck_opts* opts,
     }
     ORTH_HIP(launch_prescale_finish(tm, nt, partials, opts->prescale, status, s));
     ORTH_HIP(launch_prescale_scale(tm, T(P.off_scale_items), (int)P.scale_items.size(), opts->in_dtype,
-                                   opts->compute, s));
+                                   opts->compute, P.pieces, s));
     if (bf16) {
       // per step: all Gram tiles, then all update tiles (large class first)
       for (int t = 0; t < iters; ++t)
@@ -2372,7 +2395,7 @@ int vjp_forward(const VjpPlan& P, unsigned char* ws, const orth_bjorck_opts* opt
   // a vector-Jacobian product leaves the cached vectors alone
   ORTH_HIP(launch_prescale_finish(tm, n, partials, opts->prescale, status, s, to_output ? 1 : 0));
   ORTH_HIP(launch_prescale_scale(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->in_dtype,
-                                 opts->compute, s));
+                                 opts->compute, P.pieces, s));
   for (int t = 0; t < T; ++t) {
     ORTH_HIP(launch_list(ws, P.off_f_gram, P.f_gram, "vjp_fwd_gram_f32", s, t));
     for (int cls = 1; cls >= 0; --cls)
@@ -2591,7 +2614,8 @@ int orth_orthogonalize_vjp_batched(const orth_vjp_mat* mats, int32_t n, const or
   float* gmax = P.f32 ? reinterpret_cast<float*>(ws + P.off_gmax) : nullptr;
   if (gmax)
     ORTH_HIP(launch_vjp_grad_max(tm, TI(P.off_partial_items), (int)P.partial_items.size(), opts->out_dtype, gmax, s));
-  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, gmax, s));
+  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, gmax,
+                                P.pieces, s));
   for (int b = 0; b < T; ++b) {
     const int t = T - 1 - b, par = b & 1;
     ORTH_HIP(launch_list(ws, P.off_b_s[par], P.b_s[par], "vjp_s_f32", s, t));

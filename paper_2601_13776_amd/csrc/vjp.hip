@@ -56,7 +56,6 @@ __device__ inline int grad_exp(const TiledMat& d, const float* gmax, int m) {
   const int e = (int)(__float_as_uint(v) >> 23) - 127;
   return e < -120 ? -120 : e > 120 ? 120 : e;
 }
-__device__ inline float pow2(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // gmax[m] = max |dL/d(output)| (NaN ignored; a 64 x 64 tile of the caller's
 // layout per block).  One read of the gradient, HBM-bound.
@@ -96,11 +95,11 @@ __global__ __launch_bounds__(256) void vjp_grad_max_kernel(const TiledMat* __res
 
 __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __restrict__ mats,
                                                             const TileItem* __restrict__ items, int gout_dtype,
-                                                            const float* __restrict__ gmax) {
+                                                            const float* __restrict__ gmax, int pieces) {
   __shared__ float tile[TB][TB + 1];
   const TileItem it = items[blockIdx.x];
   const TiledMat& d = mats[it.mat];
-  const float gs = pow2(-grad_exp(d, gmax, it.mat));
+  const float gs = pow2f(-grad_exp(d, gmax, it.mat));
   const int R = it.ti * TB, C = it.tj * TB;  // tile origin in the tall padded layout
   float* y = d.gy[0];
   uint16_t* yc = static_cast<uint16_t*>(d.yc[0]);
@@ -139,7 +138,17 @@ __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __re
     if (yc) gst_u16(yc, off, f32_to_bf16(tile[a][b]));
     // fp32 products: the transpose too, Np x Mp (consecutive threads along
     // a, so its rows are written coalesced)
-    if (yt) gst_f32(yt, (int64_t)(C + a) * d.Mp + R + b, tile[b][a]);
+    if (yt && !pieces) gst_f32(yt, (int64_t)(C + a) * d.Mp + R + b, tile[b][a]);
+  }
+  if (yt && pieces) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int u = threadIdx.x + 256 * h, a = u >> 3, b = (u & 7) * 8;
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = tile[b + i][a];
+      store_pieces8(yt + (int64_t)(C + a) * d.Mp + R + b, v, 1.f);
+    }
   }
 }
 
@@ -213,7 +222,7 @@ __global__ __launch_bounds__(256) void vjp_writeout_kernel(const TiledMat* __res
   const float* gy = d.gy[d.gy_final];
   const int st = status[d.status_index];
   const float inv = *d.inv_norm;
-  const float us = pow2(grad_exp(d, gmax, it.mat));   // undoes load_grad's scale
+  const float us = pow2f(grad_exp(d, gmax, it.mat));   // undoes load_grad's scale
   const bool spec = prescale == ORTH_PRESCALE_SPECTRAL;
   const bool frob = prescale == ORTH_PRESCALE_FROBENIUS || spec;   // a term in W
   const float dscale = st != ORTH_MAT_OK ? 0.f : spec ? (float)d.sb[SB_DSCALE] : (float)(*d.dot) * inv;
@@ -287,10 +296,11 @@ hipError_t launch_vjp_grad_max(const TiledMat* mats, const TileItem* items, int 
 }
 
 hipError_t launch_vjp_load_grad(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype,
-                                const float* gmax, hipStream_t s) {
+                                const float* gmax, int pieces, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   timing_begin("vjp_load_grad", s);
-  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax);
+  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax,
+                     pieces);
   hipError_t e = hipGetLastError();
   timing_end("vjp_load_grad", s);
   return e;

@@ -298,7 +298,7 @@ hipError_t launch_prescale_finish(const TiledMat* mats, int n, const double*, in
   table(mats, n, "launch_prescale_finish");
   return launched();
 }
-hipError_t launch_prescale_scale(const TiledMat*, const TileItem* items, int n, int, int, hipStream_t) {
+hipError_t launch_prescale_scale(const TiledMat*, const TileItem* items, int n, int, int, int, hipStream_t) {
   table(items, n, "launch_prescale_scale");
   return launched();
 }
@@ -327,7 +327,8 @@ hipError_t launch_vjp_grad_max(const TiledMat*, const TileItem* items, int n, in
   table(gmax, 1, "launch_vjp_grad_max (slots)");
   return launched();
 }
-hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, const float*, hipStream_t) {
+hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, const float*, int,
+                                hipStream_t) {
   table(items, n, "launch_vjp_load_grad");
   return launched();
 }

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import bjorck, bjorck_grad, checks
+from oracle import bjorck, bjorck_grad, checks, expo, spectral
 from paper_2601_13776_amd import orth
 
 pytestmark = pytest.mark.gpu
@@ -123,3 +123,38 @@ def test_gradient_nonfinite():
         orth.orth_orthogonalize_vjp_batched(ws, g, out, 4)
         assert not torch.isfinite(out[0]).all()
         assert torch.equal(out[1], ref[1])
+
+
+# values that half cannot hold: the estimate of sigma misses a heavy block
+# (the cached vector has no part in it), so the iterates of a few steps, E
+# and the powers leave the half pieces' range.  Such runs are stored as fp32
+# values, the first of each 8 with 18 bits (2^-19 relative); a step cubes the
+# iterate, so k steps carry 3^k 2^-19 / sqrt(8) of it.
+def _heavy(c, heavy):
+    m = _rand(20, c, c)
+    m[:, -heavy:] = 0.0
+    m[-heavy:, :] = 0.0
+    m[-heavy:, -heavy:] = 1000.0 * _rand(21, heavy, heavy)
+    u = _rand(22, c)
+    u[-heavy:] = 0.0
+    return m, u
+
+
+@pytest.mark.parametrize("c,heavy,iters", [(200, 6, 1), (300, 10, 2), (129, 3, 2), (300, 10, 3)])
+def test_diverging_spectral(c, heavy, iters):
+    m, u = _heavy(c, heavy)
+    got = _run([m], iters, prescale="spectral", u=torch.from_numpy(u.copy()).to(DEV))[0]
+    ref, _, _ = spectral.bjorck_spectral(m.astype(np.float64), u.astype(np.float64), iters, 1)
+    assert np.abs(ref).max() > 200
+    assert checks.relative_difference(got, ref) <= TOL + 3 ** iters * 2.0 ** -20.5
+
+
+@pytest.mark.parametrize("c,heavy,terms", [(512, 2, 8), (450, 2, 9), (2000, 2, 12)])
+def test_exp_map_poor_sigma(c, heavy, terms):
+    m, u = _heavy(c, heavy)
+    w = torch.from_numpy(m).to(DEV)
+    out = torch.empty_like(w)
+    orth.orth_exp_map_batched([w], [out], terms, torch.from_numpy(u.copy()).to(DEV), 1)
+    ref, _ = expo.exp_map(m.astype(np.float64), terms, u.astype(np.float64))
+    assert np.abs(ref).max() > 65504
+    assert checks.relative_difference(out.cpu().numpy().astype(np.float64), ref) <= TOL + terms * 2.0 ** -20.5
