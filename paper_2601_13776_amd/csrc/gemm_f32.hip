@@ -551,13 +551,14 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
           }
           if (item.dst2) put_pieces(t, true, item.dst2 + item.d2_step * st, item.ld2, jbase, ibase, N, M, M);
         } else if (item.epi == EPI_SERIES) {
+          const float g = pow2f(item.src ? series_exp(gld_f32(item.src, 0)) : 0);
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int i = ibase + acc_row(r, lane);
-            t[r] = item.beta * v[r];
+            t[r] = item.beta * g * v[r];
             // each element belongs to one item of the launch
             if (i < M && j < N)
-              gst_f32(item.dst2, (int64_t)i * item.ld2 + j, gld_f32(item.dst2, (int64_t)i * item.ld2 + j) + t[r]);
+              gst_f32(item.dst2, (int64_t)i * item.ld2 + j, gld_f32(item.dst2, (int64_t)i * item.ld2 + j) + t[r] * g);
           }
           if (C) put_pieces(t, false, C, ldc, ibase, jbase, M, (int)ldc, N);
         } else {   // EPI_GRAM_E, EPI_NEG
@@ -621,20 +622,6 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
               for (int k = 0; k < 4; ++k)
                 if (i + k < M) gst_f32(d, k, e[4 * q + k]);
             }
-          }
-        }
-      } else if (epi == EPI_SERIES) {
-        float* dst2 = item.dst2;
-        const int64_t ld2 = item.ld2;
-        const float beta = item.beta;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = ibase + acc_row(r, lane);
-          if (i < M && j < N) {
-            const float p = beta * v[r];
-            gst_f32(C, (int64_t)i * ldc + j, p);
-            // each element belongs to one item of the launch
-            gst_f32(dst2, (int64_t)i * ld2 + j, gld_f32(dst2, (int64_t)i * ld2 + j) + p);
           }
         }
       } else {  // EPI_UPDATE

@@ -1527,8 +1527,9 @@ struct ExpPlan {
   std::vector<GemmPair> pairs;                // conv: operand pairs of all steps
   std::vector<TapItem> scatter;               // conv: E taps -> OIHW
   int64_t max_elems = 0, max_init = 0, max_scatter = 0;
+  std::vector<float> amax;                    // conv: a slot per layer for max |L|, zero when the call starts
   size_t off_items = 0, off_mats = 0, off_partial = 0, off_writeout = 0, off_power[2] = {}, off_pairs = 0,
-         off_scatter = 0, off_partials = 0, off_inv = 0, off_status = 0;
+         off_amax = 0, off_scatter = 0, off_partials = 0, off_inv = 0, off_status = 0;
   std::vector<size_t> off_steps;
   size_t table_bytes = 0, total_bytes = 0;
 };
@@ -1680,6 +1681,7 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
   int max_p = 1;
   for (int i = 0; i < n; ++i) max_p = std::max(max_p, d[i].terms);
   P.steps.assign(max_p - 1, {});
+  P.amax.assign(n, 0.f);
   // two passes: count tables, then lay out tables followed by buffers
   for (int pass = 0; pass < 2; ++pass) {
     Arena A;
@@ -1687,6 +1689,7 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
       P.off_items = A.take(sizeof(ExpItem) * P.items.size());
       P.off_pairs = A.take(sizeof(GemmPair) * P.pairs.size());
       P.off_scatter = A.take(sizeof(TapItem) * P.scatter.size());
+      P.off_amax = A.take(sizeof(float) * P.amax.size());
       P.off_steps.resize(P.steps.size());
       for (size_t k = 0; k < P.steps.size(); ++k) P.off_steps[k] = A.take(GemmList::bound(P.steps[k].size()));
       P.table_bytes = align_up(A.off);
@@ -1702,12 +1705,22 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
       const orth_conv_exp_desc& L = d[li];
       const int c = L.channels, k = L.k, p = L.terms, S = p * (k - 1) + 1;
       const int64_t cc = (int64_t)c * c;
-      float* lt = fbuf((int64_t)k * k * cc);
+      // taps as half pieces, rows padded to whole k-steps with zeros: those
+      // of L (the first power) and of the powers that a product reads.  The
+      // fp32 L is read only until lt is written.
+      const int cp = (int)round_up(c, 32);
+      const int Sq = std::max((p - 1) * (k - 1) + 1, k);
+      const int64_t ccp = (int64_t)c * cp;
       float* acc = fbuf((int64_t)S * S * cc);
-      float* q[2] = {p > 1 ? fbuf((int64_t)S * S * cc) : nullptr, p > 2 ? fbuf((int64_t)S * S * cc) : nullptr};
+      float* lt = p > 1 ? fbuf((int64_t)k * k * ccp) : nullptr;
+      float* q[2] = {p > 2 ? fbuf((int64_t)Sq * Sq * ccp) : nullptr, fbuf((int64_t)Sq * Sq * ccp)};
+      float* amax = reinterpret_cast<float*>(dev(P.off_amax)) + li;
       ExpItem e{};
       e.in = L.kernel;
-      e.a = lt;
+      e.a = q[1];
+      e.p0 = lt;
+      e.ld_p = cp;
+      e.amax = amax;
       e.out = acc;
       e.c = c;
       e.k = k;
@@ -1728,18 +1741,20 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
                 const int py = y - r, px = x - t;
                 if (py < 0 || py >= sp || px < 0 || px >= sp) continue;
                 GemmPair gp{};
-                gp.A = prev + (int64_t)(py * sp + px) * cc;
-                gp.B = lt + (int64_t)((k - 1 - r) * k + (k - 1 - t)) * cc;   // L_{r,t}^T = -L_{k-1-r,k-1-t}
-                gp.lda = gp.ldb = c;
-                gp.K = c;
+                gp.A = prev + (int64_t)(py * sp + px) * ccp;
+                gp.B = lt + (int64_t)((k - 1 - r) * k + (k - 1 - t)) * ccp;   // L_{r,t}^T = -L_{k-1-r,k-1-t}
+                gp.lda = gp.ldb = cp;
+                gp.K = cp;
                 P.pairs.push_back(gp);
               }
             GemmItem g{};
             g.pair_base = base;
             g.pair_count = (int)P.pairs.size() - base;
             g.M = g.N = c;
-            g.C = cur + (int64_t)(y * sj + x) * cc;
-            g.ldc = c;
+            g.C = j < p ? cur + (int64_t)(y * sj + x) * ccp : nullptr;   // (nothing reads the last power)
+            g.ldc = cp;
+            g.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(0);
+            g.src = amax;
             g.dst2 = acc + (int64_t)((y + off) * S + x + off) * cc;
             g.ld2 = c;
             g.beta = -1.f / j;
@@ -1752,6 +1767,7 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
     }
     P.total_bytes = align_up(A.off);
   }
+  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);
   (void)dtype;
 }
 }  // namespace
@@ -2953,6 +2969,7 @@ int orth_conv_exp_batched(const orth_conv_exp_desc* descs, int32_t n, int32_t dt
   put(img, P.off_items, P.items);
   put(img, P.off_pairs, P.pairs);
   put(img, P.off_scatter, P.scatter);
+  put(img, P.off_amax, P.amax);
   for (size_t k = 0; k < P.steps.size(); ++k) put(img, P.off_steps[k], P.steps[k]);
   rc = upload_tables(img, ws, s);
   if (rc) return rc;

@@ -175,6 +175,17 @@ constexpr int kIterExp = 8;
 // factorials: a poor estimate of sigma makes them large, and what they add
 // to I + ... needs no more than 2^-36 absolute.
 constexpr int kExpExp = 0;
+// The conv exponential's L has any size: its powers over their factorials
+// are stored as pieces of 2^-g times their values, with max |L| in [16, 32)
+// after scaling, so that powers may grow 2^11 times (e^9 over a few terms)
+// before runs become fp32, and what a power loses is below 2^-39 max |L|.
+__host__ __device__ inline int series_exp(float amax) {
+  if (!(amax > 0.f) || !(amax <= 3.402823466e38f)) return 0;
+  uint32_t u;
+  __builtin_memcpy(&u, &amax, 4);
+  const int e = (int)(u >> 23) - 127 - 4;
+  return e < -100 ? -100 : e > 100 ? 100 : e;
+}
 
 // ---------------------------------------------------------------------------
 // Björck batch descriptors (device-resident tables built by the host).
@@ -295,7 +306,8 @@ enum GemmEpi : int32_t {
   EPI_UPDATE = 2,    // v = src[i][j] + beta acc; C[i][j] = v; dst2[j][i] = v if dst2
   EPI_MAXDEV = 3,    // red[0] = max(red[0], |delta_ij - acc|)
   EPI_NEG = 4,       // C[i][j] = -acc  (and C[j][i] if mirror)
-  EPI_SERIES = 5     // v = beta acc; C[i][j] = v (fp32); dst2[i][j] += v (ld2)
+  EPI_SERIES = 5     // v = beta acc; C[i][j] = v (half pieces); dst2[i][j] += v (ld2).  With
+                     //   src (see series_exp): v = beta 2^g acc, dst2 += 2^g v
 };
 
 // A further operand pair of a GEMM item (same storage dtypes as the item's
@@ -507,9 +519,10 @@ struct ExpItem {
   const void* in;            // W (C x C, caller layout) or the kernel K (c x c x k x k, OIHW)
   float* a;                  // exp map: A = W - W^T (C x C); conv: L taps (k x k grid)
   float* out;                // the fp32 series accumulator (C x C, or S x S taps)
-  float* p0;                 // exp map: first power Ahat as half pieces (row stride ld_p,
-                             //   zero past c); unused for conv
+  float* p0;                 // first power (Ahat; conv: the L taps, k x k matrices of
+                             //   c x ld_p) as half pieces, row stride ld_p, zero past c
   int64_t ld_p;
+  float* amax;               // conv: receives max |L| (zero before)
   const float* inv;          // exp map: 1 / sigma of A (from the spectral pre-scaling kernels)
   int64_t ld_in;
   int32_t c;                 // C, or channels c

@@ -158,3 +158,26 @@ def test_exp_map_poor_sigma(c, heavy, terms):
     ref, _ = expo.exp_map(m.astype(np.float64), terms, u.astype(np.float64))
     assert np.abs(ref).max() > 65504
     assert checks.relative_difference(out.cpu().numpy().astype(np.float64), ref) <= TOL + terms * 2.0 ** -20.5
+
+
+# conv exponentials: channel counts at the edges of the padded rows and
+# tiles (the last one fills every compute unit with 128-tiles), series of 2
+# and 3 terms, kernels of any size; of the last three scales the powers
+# outgrow the half pieces after the first step, at once, and never
+@pytest.mark.parametrize("c,k,terms,scale", [(31, 3, 3, 0.05), (33, 5, 4, 0.1), (65, 3, 2, 0.02), (96, 1, 5, 0.05),
+                                             (512, 3, 3, 0.004), (40, 3, 4, 40.0), (16, 5, 3, 1e8),
+                                             (24, 3, 4, 1e-9)])
+def test_conv_exp_pieces(c, k, terms, scale):
+    kern = _rand(30, c, c, k, k)
+    S = terms * (k - 1) + 1
+    out = torch.full((c, c, S, S), float("nan"), device=DEV)
+    orth.orth_conv_exp_batched([dict(kernel=torch.from_numpy(kern).to(DEV), out=out, terms=terms, scale=scale)])
+    got = out.cpu().numpy().astype(np.float64)
+    ref = expo.conv_exp(kern.astype(np.float64), terms, float(np.float32(scale)))
+    tol = TOL + (terms * 2.0 ** -20.5 if scale > 1 else 0.0)
+    assert checks.relative_difference(got, ref) <= tol
+    if scale < 1e-6:   # the kernel itself, beside the identity
+        eye = np.zeros_like(ref)
+        eye[np.arange(c), np.arange(c), S // 2, S // 2] = 1.0
+        off = ~(eye > 0)
+        assert checks.relative_difference(got[off][None], ref[off][None]) <= TOL
