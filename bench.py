@@ -30,7 +30,10 @@ sys.path.insert(0, ROOT)
 from paper_2601_13776_amd import workloads as wl  # noqa: E402
 
 PEAK_BF16_TFLOPS = 2516.6   # MI355X dense bf16 MFMA
-PEAK_F32_TFLOPS = 157.3     # MI355X fp32 MFMA
+# MI355X fp32 MFMA: the yardstick of fp32 products.  They run on the 16-bit
+# matrix cores with three or six products each (ceilings of 839 and 419
+# TFLOP/s), so a fraction of this peak can exceed 1.
+PEAK_F32_TFLOPS = 157.3
 PEAK_HBM_GBS = 8000.0
 METRIC = "orthogonalized layers/sec per param step; Björck TFLOP/s as % MFMA peak"
 DEFAULT_WORKLOAD = "stress_4096x64_32x4096"

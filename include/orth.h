@@ -64,9 +64,10 @@ typedef enum {
 
 typedef enum { ORTH_F32 = 0, ORTH_BF16 = 1 } orth_dtype;
 
-/* Arithmetic of the Björck products: fp32 operands on fp32 MFMA, or
- * bfloat16 operands with fp32 accumulation (the iterate itself is always
- * kept in fp32). */
+/* Arithmetic of the Björck products: fp32 operands (each value split into
+ * 16-bit pieces that carry its 24 bits, fp32 accumulation), or bfloat16
+ * operands with fp32 accumulation (the iterate itself is always kept in
+ * fp32). */
 typedef enum { ORTH_COMPUTE_F32 = 0, ORTH_COMPUTE_BF16 = 1 } orth_compute;
 
 /* Pre-scaling of W before the iteration: none, W / ||W||_F, or W / sigma
@@ -452,7 +453,8 @@ typedef struct {
  * c = cin/g, pl = floor((d (k-1) + 1 - s) / 2); transposed: the adjoint of
  * that map.  For an orthogonal kernel with cout/g <= c s^2 the forward map
  * has orthonormal rows, so the transposed map preserves norms and the
- * forward map inverts it.  fp32 arithmetic on fp32 MFMA.
+ * forward map inverts it.  fp32 arithmetic: 16-bit MFMA on values split
+ * into pieces for k <= 3, fp32 MFMA otherwise.
  * Errors: the geometry errors of orth_aoc_param_shapes, ORTH_EINVAL for
  * NULL pointers, batch/height/width < 1, H or W not divisible by the
  * stride, x == y, or an unknown dtype.
