@@ -511,9 +511,6 @@ struct GemmList {
   int64_t pending64 = 0;          // their count of 64-tiles
   GemmItem last{};   // items.back() with its tile and mirror fields cleared
   GemmRun run{GEMM_BF16X3, 64, {0, 0, 0}, GEMM_PRE_NONE};
-  // Products of large operands (the series): an XCD works on 64 neighbouring
-  // tiles at a time.  See deal_to_xcds.
-  bool by_xcd = false;
   // at most this many tiles (the count with 64-tiles)
   size_t size() const { return tiles.size() + (size_t)pending64; }
   void clear() {
@@ -538,38 +535,15 @@ struct GemmList {
     });
     run.n[0] = run.n[1] = run.n[2] = 0;
     for (const GemmTile& t : tiles) ++run.n[mode(items[t.item])];
-    if (by_xcd) deal_to_xcds();
-    by_xcd = false;   // dealt once
-  }
-  // Blocks go to the 8 XCDs in turn, and an XCD holds 64 tiles of 128 at a
-  // time (32 compute units, two each).  So of every 512 tiles of the list
-  // each XCD takes 64 consecutive ones, which advance through K together:
-  // 8 x 8 tiles of a product share 16 operand panels in that XCD's L2, where
-  // dealt singly the 64 had up to 65 (the A panels of 8 rows in 8 products).
-  // Exponential map of 128^2 to 2048^2, 12 terms: 4.91 -> 4.85 ms.
-  void deal_to_xcds() {
-    std::vector<GemmTile> out(tiles.size());
-    for (size_t b = 0; b < tiles.size(); b += 512) {
-      const size_t r = std::min<size_t>(512, tiles.size() - b), base = r / 8, more = r % 8;
-      for (size_t i = 0; i < r; ++i) {
-        const size_t q = i % 8;
-        out[b + i] = tiles[b + q * base + std::min(q, more) + i / 8];
-      }
-    }
-    tiles.swap(out);
   }
   void finalize() {
     if (pending.empty()) return;
     int64_t n128 = 0;
     for (int32_t idx : pending) n128 += tiles_of(items[idx].M, 128) * tiles_of(items[idx].N, 128);
     run.tile = gemm_tile_edge(n128);
-    const int group = by_xcd ? 8 : 1;   // rows of tiles taken together
-    for (int32_t idx : pending) {
-      const int ta = (int)tiles_of(items[idx].M, run.tile), tb = (int)tiles_of(items[idx].N, run.tile);
-      for (int a0 = 0; a0 < ta; a0 += group)
-        for (int b = 0; b < tb; ++b)
-          for (int a = a0; a < std::min(a0 + group, ta); ++a) tiles.push_back(GemmTile{idx, a, b, 0});
-    }
+    for (int32_t idx : pending)
+      for (int a = 0; a < tiles_of(items[idx].M, run.tile); ++a)
+        for (int b = 0; b < tiles_of(items[idx].N, run.tile); ++b) tiles.push_back(GemmTile{idx, a, b, 0});
     pending.clear();
     pending64 = 0;
   }
@@ -1684,11 +1658,7 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
       gemm_tiles(g, P.steps[k - 2]);
     }
   }
-  for (auto& g : P.steps) {
-    g.run = ranged_run(true, 0, GEMM_PRE_BOTH);   // |Ahat| is about 1
-    g.by_xcd = true;
-    longest_first(g);
-  }
+  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);   // |Ahat| is about 1
   P.total_bytes = align_up(A.off);
 }
 
@@ -1797,11 +1767,7 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
     }
     P.total_bytes = align_up(A.off);
   }
-  for (auto& g : P.steps) {
-    g.run = ranged_run(true, 0, GEMM_PRE_BOTH);
-    g.by_xcd = true;
-    longest_first(g);
-  }
+  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);
   (void)dtype;
 }
 }  // namespace
