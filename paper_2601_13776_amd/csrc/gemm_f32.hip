@@ -228,7 +228,7 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
   uint4 raw[2][2][2];      // [register set][operand][half]
   float scl[2][2];
   PairView pv;
-  uint32_t voff[2];        // this thread's byte offset from the step's first value
+  uint32_t voff[2];        // this thread's byte offset from the step's first value (row strides up to 2^23)
   const char* at[2];       // the step's first value of the tile's rows
   int64_t astep[2];
   int pair = -1, left = 0; // whole steps of the pair that are not loaded yet

@@ -519,9 +519,14 @@ struct GemmList {
     pending.clear();
     pending64 = 0;
   }
-  // how every operand of the product is stored
+  // how every operand of the product is stored; GEMM_ANY also takes row
+  // strides past which a tile's byte offsets no longer fit the 32 bits of
+  // the other two modes (only a Gram check's, the caller's own, can be so
+  // long)
+  static constexpr int64_t kMaxLd = (int64_t)1 << 23;   // 128 rows of 4 bytes: 2^32
   static GemmMode mode(const GemmItem& it) {
     if (it.a_dtype != ORTH_F32 || it.b_dtype != ORTH_F32) return GEMM_ANY;
+    if (std::max(it.lda, it.ldb) > kMaxLd) return GEMM_ANY;
     if ((it.trans & GEMM_ANY_TRANS) == 0) return GEMM_ROWS;   // further pairs are row-major too
     if ((it.trans & GEMM_ANY_TRANS) == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
       return GEMM_KMAJOR;
@@ -3041,7 +3046,7 @@ void gram_check_items(const orth_check_args* a, float* out, GemmList& items) {
         g.a_dtype = g.b_dtype = a->mat_dtype;
         g.trans = tall ? GEMM_A_TRANS | GEMM_B_TRANS : 0;
         g.epi = EPI_MAXDEV;
-        g.red = out + i;
+        g.red = out ? out + i : nullptr;   // (sizing: no output yet)
         items.push_back(g);
       }
   }

@@ -10,6 +10,8 @@
 //   conv  <dtype> <expect> <n> cin cout k s d g ...
 //   convvjp <dtype> <expect> <n> cin cout k s d g ...
 //   convsave <dtype> <expect> <n> cin cout k s d g ...
+//   gram  <dtype> <mode> <n> r c ld ...   (a Gram check; all its tiles must be
+//         planned as operands of that GemmMode: 0 rows, 1 k-major, 2 any)
 //   selftest <which>   (a planted violation of the stand-ins' checks: must abort)
 // `expect` is the orth_status the call must return (for the workspace query
 // and the call); data buffers are fake device allocations of the right size.
@@ -34,6 +36,7 @@ void* stub_dev_alloc(size_t bytes);
 void stub_reset(void);
 long stub_launches(void);
 long stub_launches_total(void);
+int stub_gemm_tiles(int mode);
 void stub_selftest(int which);
 }
 
@@ -160,6 +163,32 @@ void run_conv(std::istringstream& in, const std::string& kind, int line) {
   }
 }
 
+void run_gram(std::istringstream& in, int line) {
+  orth_check_args a{};
+  int mode = 0;
+  a.mode = ORTH_CHECK_GRAM;
+  in >> a.mat_dtype >> mode >> a.n_mats;
+  std::vector<orth_mat> mats(a.n_mats);
+  for (orth_mat& m : mats) {
+    m = orth_mat{};
+    in >> m.rows >> m.cols >> m.ld_in;
+    m.in = stub_dev_alloc((size_t)m.rows * m.ld_in * esz(a.mat_dtype));
+  }
+  a.mats = mats.data();
+  float* out = static_cast<float*>(stub_dev_alloc(4 * (size_t)a.n_mats));
+  size_t need = 0;
+  check(orth_check_workspace_size(&a, &need), ORTH_OK, line, "workspace size");
+  void* ws = stub_dev_alloc(need);
+  stub_reset();
+  check(orth_check_norm(&a, out, ws, need, nullptr), ORTH_OK, line, "gram");
+  for (int k = 0; k < 3; ++k)
+    if ((stub_gemm_tiles(k) > 0) != (k == mode)) {
+      std::printf("FAIL line %d gram: %d tiles of mode %d, expected all of mode %d\n", line, stub_gemm_tiles(k), k,
+                  mode);
+      ++g_fail;
+    }
+}
+
 // one command line; returns false for a blank line or a comment
 bool run_line(const std::string& text, int line, bool threaded) {
   std::istringstream in(text);
@@ -169,6 +198,8 @@ bool run_line(const std::string& text, int line, bool threaded) {
     run_ortho(in, kind, line);
   else if (kind == "conv" || kind == "convvjp" || kind == "convsave")
     run_conv(in, kind, line);
+  else if (kind == "gram")
+    run_gram(in, line);
   else if (kind == "selftest") {
     int which = 0;
     in >> which;

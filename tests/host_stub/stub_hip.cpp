@@ -15,6 +15,7 @@
 // stand-ins are safe to call from several threads at once.
 #include <sys/mman.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -40,6 +41,7 @@ std::map<uintptr_t, uintptr_t> g_dev;       // registered device ranges [begin, 
 thread_local std::map<uintptr_t, uintptr_t> g_written;
 long g_launches = 0;
 thread_local long t_launches = 0;           // launches of the calling thread
+thread_local int t_gemm_tiles[3] = {};      // tiles by GemmMode of the thread's last fp32 product launch
 long g_copies = 0;
 unsigned char* g_arena = nullptr;           // reserved PROT_NONE address space
 size_t g_arena_size = 0, g_arena_used = 0;
@@ -148,6 +150,9 @@ long stub_launches_total(void) {
   std::lock_guard<std::mutex> lk(g_mu);
   return g_launches;
 }
+
+// Tiles of one GemmMode in the calling thread's last fp32 product launch.
+int stub_gemm_tiles(int mode) { return t_gemm_tiles[mode]; }
 
 // Checks of the checks: 0 launches from a table no copy wrote, 1 copies
 // outside device memory; each must end the process with a violation.
@@ -318,6 +323,7 @@ hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const G
   if (run.split == GEMM_F16X2 && run.n[GEMM_KMAJOR] + run.n[GEMM_ANY] > 0)
     violation("two pieces planned for other than row-major products", name, 0, 0);
   const int n_tiles = run.n[0] + run.n[1] + run.n[2];
+  std::copy(run.n, run.n + 3, t_gemm_tiles);
   if (n_tiles > 0) table(items, 1, name);
   table(tiles, n_tiles, name);
   return launched();

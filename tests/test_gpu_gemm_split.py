@@ -47,6 +47,19 @@ def test_big_tile_lists(shape, n, prescale):
         assert checks.relative_difference(got[i], ref) <= TOL
 
 
+# a strided view whose row offsets within a tile exceed 32 bits (in bytes):
+# rows and k-major; each row of the tile is its own
+@pytest.mark.parametrize("rows,cols,ld", [(64, 100, 17_100_000), (72, 40, 36_000_000)])
+def test_gram_of_long_strides(rows, cols, ld):
+    m = _rand(12, rows, cols)
+    buf = torch.zeros(rows, ld, device=DEV)
+    view = buf[:, :cols]
+    view.copy_(torch.from_numpy(m))
+    got = float(orth.orth_check_norm_gram([view])[0])
+    ref = checks.gram_deviation(m.astype(np.float64))
+    assert abs(got - ref) <= TOL * max(1.0, ref)
+
+
 # light rows keep their own relative accuracy beside rows 2^10 times larger
 # (the half pieces' range)
 def test_row_scales():

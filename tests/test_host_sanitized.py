@@ -106,6 +106,12 @@ def workload_spec():
     lines.append("ortho 4 1 1 1 1 256 0 4 1100 1030 1030 1100 33 17 2048 1000")
     lines.append("ortho 4 1 1 1 1 128 0 3 4096 4096 300 700 1 1")
     lines.append("vjp 4 1 1 2 16 256 0 0 3 1100 1030 64 32 17 33")
+    lines.append("# Gram checks: row strides whose offsets within a tile fit 32 bits, and longer ones")
+    lines.append(f"gram 0 0 2 64 100 {1 << 23} 7 9 9")
+    lines.append(f"gram 0 1 1 100 64 {1 << 23}")
+    lines.append(f"gram 0 2 1 64 100 {(1 << 23) + 1}")
+    lines.append("gram 0 2 2 64 100 17043522 64 40 35800000")
+    lines.append("gram 1 2 1 64 100 100")
     lines.append("# error paths")
     lines.append("ortho 4 0 0 1 1 0 1 2 0 4 8 8")            # rows 0
     lines.append("ortho 4 0 0 1 1 64 1 1 8 8")               # tile 64
