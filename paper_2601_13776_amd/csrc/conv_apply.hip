@@ -293,22 +293,10 @@ struct StageGeom {
 };
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
-typedef float f32x2v __attribute__((ext_vector_type(2)));
 // 16- and 8-byte global loads at element alignment (gfx950 needs no more)
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
-__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {
-  const f32x2v v{a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2v));
-}
-__device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
-  h = cvt2_bf16(a, b);
-  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
-  m = cvt2_bf16(ra, rb);
-  l = cvt2_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
-}
 
 // A wave's 32 x 32 block with fp32 MFMA: this lane's channel `row` of the
 // group (as MFMA row) and output pixel (as column), the original formula.

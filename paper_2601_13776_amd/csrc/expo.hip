@@ -26,7 +26,6 @@ __global__ __launch_bounds__(256) void exp_skew_kernel(const ExpItem* __restrict
   const int c = it.c, k = it.k;
   const int64_t cc = (int64_t)c * c;
   const int64_t total = conv ? (int64_t)k * k * cc : cc;
-  float m = 0.f;
   for (int64_t e = blockIdx.x * 256 + threadIdx.x; e < total; e += (int64_t)gridDim.x * 256) {
     if (!conv) {
       const int i = (int)(e / c), j = (int)(e % c);
@@ -42,37 +41,19 @@ __global__ __launch_bounds__(256) void exp_skew_kernel(const ExpItem* __restrict
       const float v = load_as_f32(it.in, ((int64_t)o * c + i) * kk + a * k + b, in_dtype) -
                       load_as_f32(it.in, ((int64_t)i * c + o) * kk + (k - 1 - a) * k + (k - 1 - b), in_dtype);
       it.a[e] = it.scale * v;
-      m = fmaxf(m, fabsf(it.scale * v));
-    }
-  }
-  if (conv) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
-    // one atomic per block at most, and none where the slot already holds
-    // more (conv exponentials of 64 to 512 channels with one per wave: 10.7 ms
-    // instead of 10.1)
-    __shared__ float red[4];
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-      unsigned int* slot = reinterpret_cast<unsigned int*>(it.amax);
-      if (__float_as_uint(m) > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-        atomicMax(slot, __float_as_uint(m));
     }
   }
 }
 
-// rows of a (c columns) scaled by f and then as pieces of 2^e times that,
-// zeros up to ld
-__device__ inline void rows_to_pieces(const float* a, int64_t rows, int c, float* p, int64_t ld, float f, int e) {
+// rows of a (c columns) scaled by f, zeros up to ld
+__device__ inline void padded_rows(const float* a, int64_t rows, int c, float* p, int64_t ld, float f) {
   const int64_t runs = ld / 8;
   for (int64_t u = blockIdx.x * 256 + threadIdx.x; u < rows * runs; u += (int64_t)gridDim.x * 256) {
     const int64_t i = u / runs, j = (u - i * runs) * 8;
     float v[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) v[k] = j + k < c ? a[i * c + j + k] * f : 0.f;
-    store_pieces8(p + i * ld + j, v, pow2f(e));
+    store8_f32(p, i * ld + j, ORTH_F32, v);
   }
 }
 
@@ -86,7 +67,7 @@ __global__ __launch_bounds__(256) void exp_init_kernel(const ExpItem* __restrict
       const float ah = it.a[e] * inv;
       it.out[e] = (e / c == e % c ? 1.f : 0.f) + ah;
     }
-    rows_to_pieces(it.a, c, c, it.p0, it.ld_p, inv, kExpExp);
+    padded_rows(it.a, c, c, it.p0, it.ld_p, inv);
     return;
   }
   const int S = it.size, k = it.k, mid = (S - 1) / 2, off = (S - k) / 2;
@@ -100,7 +81,7 @@ __global__ __launch_bounds__(256) void exp_init_kernel(const ExpItem* __restrict
     if (ly >= 0 && ly < k && lx >= 0 && lx < k) v += it.a[(int64_t)(ly * k + lx) * cc + oi];
     it.out[e] = v;
   }
-  if (it.p0) rows_to_pieces(it.a, (int64_t)k * k * c, c, it.p0, it.ld_p, pow2f(-series_exp(*it.amax)), 0);
+  if (it.p0) padded_rows(it.a, (int64_t)k * k * c, c, it.p0, it.ld_p, 1.f);
 }
 
 unsigned grid_x(int64_t max_elems) {

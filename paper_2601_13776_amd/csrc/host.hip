@@ -497,9 +497,7 @@ static_assert(sizeof(GemmItem) % 8 == 0 && sizeof(GemmItem) == 8 * 8 + 14 * 8 + 
               "GemmItem must have no padding: items are compared bytewise");
 // Tile edge of a list whose products make n128 tiles of 128: those halve
 // the LDS traffic and splitting work per product, but a 64-tile list has
-// four times the tiles to fill the 256 compute units with (2048 x 1024,
-// K = 512, two pieces: 16.2 us with 128 tiles of 128, 14.2 us with 512 of
-// 64; 2048^3: 61 us with 256 of 128, 80 us with 1024 of 64).
+// four times the tiles to fill the 256 compute units with.
 constexpr int64_t kTile128Min = 256;
 inline int gemm_tile_edge(int64_t n128) { return n128 >= kTile128Min ? 128 : 64; }
 inline int64_t tiles_of(int64_t rows, int edge) { return (rows + edge - 1) / edge; }
@@ -510,7 +508,7 @@ struct GemmList {
   std::vector<int32_t> pending;   // add_all products without tiles yet
   int64_t pending64 = 0;          // their count of 64-tiles
   GemmItem last{};   // items.back() with its tile and mirror fields cleared
-  GemmRun run{GEMM_BF16X3, 64, {0, 0, 0}, GEMM_PRE_NONE};
+  GemmRun run{64, {0, 0, 0}};
   // at most this many tiles (the count with 64-tiles)
   size_t size() const { return tiles.size() + (size_t)pending64; }
   void clear() {
@@ -527,8 +525,8 @@ struct GemmList {
   static GemmMode mode(const GemmItem& it) {
     if (it.a_dtype != ORTH_F32 || it.b_dtype != ORTH_F32) return GEMM_ANY;
     if (std::max(it.lda, it.ldb) > kMaxLd) return GEMM_ANY;
-    if ((it.trans & GEMM_ANY_TRANS) == 0) return GEMM_ROWS;   // further pairs are row-major too
-    if ((it.trans & GEMM_ANY_TRANS) == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
+    if (it.trans == 0) return GEMM_ROWS;   // further pairs are row-major too
+    if (it.trans == (GEMM_A_TRANS | GEMM_B_TRANS) && it.K2 <= 0 && !it.pair_count && it.M % 4 == 0 && it.N % 4 == 0)
       return GEMM_KMAJOR;
     return GEMM_ANY;
   }
@@ -614,17 +612,6 @@ hipError_t launch_list(const unsigned char* ws, size_t off, const GemmList& g, c
                          reinterpret_cast<const GemmTile*>(ws + off + g.items_bytes()), g.run, name, s, step, pairs);
 }
 
-// Products of operands of known range (iterates scaled by Frobenius or
-// spectral pre-scaling, E, Ahat, scaled gradients) take two half pieces, and
-// what only products read (the transposed iterates, E, S', the powers) is
-// stored as pieces (stored once, loaded once per tile of a row or column, so
-// splitting at the store does 1/8 to 1/32 of the work at 512^2 to 2048^2).
-// Without pre-scaling nothing is known about the range: three bfloat16
-// pieces of fp32 buffers.
-inline GemmRun ranged_run(bool ranged, int64_t n128, GemmPre pre) {
-  return GemmRun{ranged ? GEMM_F16X2 : GEMM_BF16X3, gemm_tile_edge(n128), {0, 0, 0}, ranged ? pre : GEMM_PRE_NONE};
-}
-
 }  // namespace
 
 // ---------------------------------------------------- orthogonalize plan --
@@ -657,7 +644,6 @@ struct OrthoPlan {
   size_t off_power[2] = {0, 0};
   size_t off_partials = 0, off_inv = 0, off_status = 0;
   size_t table_bytes = 0, total_bytes = 0;
-  bool pieces = false;  // fp32 products: transposed iterates and E stored as half pieces
   int n_out_iter = 0;   // tiled matrices whose output buffer holds the fp32 iterate
 };
 
@@ -849,8 +835,7 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
 
   auto dev = [&](size_t off) -> unsigned char* { return ws ? ws + off : nullptr; };
 
-  // fp32 products: tile edges and pieces of the step's two lists
-  const bool two_pieces = o->prescale != ORTH_PRESCALE_NONE;
+  // fp32 products: tile edges of the step's two lists
   int64_t g128 = 0, u128 = 0;
   for (const MatPlan& q : P.mp)
     if (q.bucket == TILED_F32) {
@@ -858,9 +843,8 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
       g128 += tn * (tn + 1) / 2;
       u128 += tiles_of(q.Mp, 128) * tn;
     }
-  P.f32_gram.run = ranged_run(two_pieces, g128, GEMM_PRE_BOTH);
-  P.f32_update[0].run = P.f32_update[1].run = ranged_run(two_pieces, u128, GEMM_PRE_RIGHT);
-  P.pieces = two_pieces;
+  P.f32_gram.run.tile = gemm_tile_edge(g128);
+  P.f32_update[0].run.tile = P.f32_update[1].run.tile = gemm_tile_edge(u128);
 
   // per-matrix buffers and descriptors
   int part_base = 0;
@@ -965,10 +949,6 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
         gi.ti = g.ti;
         gi.tj = g.tj;
         gi.a_dtype = gi.b_dtype = ORTH_F32;
-        if (two_pieces) {
-          gi.exps = gemm_exps(kIterExp, kIterExp);
-          gi.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kIterExp);
-        }
         gi.epi = EPI_GRAM_E;
         gi.mirror = g.ti != g.tj;
         P.f32_gram.push_back(gi);
@@ -992,10 +972,6 @@ void build_ortho_plan(const orth_mat* mats, int32_t n, const orth_bjorck_opts* o
           gi.ti = u.ti;
           gi.tj = u.tj;
           gi.a_dtype = gi.b_dtype = ORTH_F32;
-          if (two_pieces) {
-            gi.exps = gemm_exps(kIterExp, kIterExp);
-            gi.trans = GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kIterExp);
-          }
           gi.epi = EPI_UPDATE;
           gi.beta = o->beta;
           P.f32_update[par].push_back(gi);
@@ -1532,9 +1508,8 @@ struct ExpPlan {
   std::vector<GemmPair> pairs;                // conv: operand pairs of all steps
   std::vector<TapItem> scatter;               // conv: E taps -> OIHW
   int64_t max_elems = 0, max_init = 0, max_scatter = 0;
-  std::vector<float> amax;                    // conv: a slot per layer for max |L|, zero when the call starts
   size_t off_items = 0, off_mats = 0, off_partial = 0, off_writeout = 0, off_power[2] = {}, off_pairs = 0,
-         off_amax = 0, off_scatter = 0, off_partials = 0, off_inv = 0, off_status = 0;
+         off_scatter = 0, off_partials = 0, off_inv = 0, off_status = 0;
   std::vector<size_t> off_steps;
   size_t table_bytes = 0, total_bytes = 0;
 };
@@ -1595,7 +1570,7 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
     const orth_mat& m = mats[i];
     const int C = m.rows;
     const int64_t cc = (int64_t)C * C;
-    // powers as half pieces, rows padded to whole k-steps with zeros
+    // powers with rows padded to whole k-steps with zeros
     const int Cp = (int)round_up(C, 32);
     float* a = fbuf((int64_t)C * Cp);
     float* ahat = fbuf((int64_t)C * Cp);
@@ -1656,14 +1631,11 @@ void build_exp_plan(const orth_mat* mats, int32_t n, const orth_exp_opts* o, Exp
       g.ldc = Cp;
       g.dst2 = acc;
       g.ld2 = C;
-      g.exps = gemm_exps(kExpExp, kExpExp);
-      g.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(kExpExp);
       g.beta = -1.f / k;
       g.epi = EPI_SERIES;
       gemm_tiles(g, P.steps[k - 2]);
     }
   }
-  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);   // |Ahat| is about 1
   P.total_bytes = align_up(A.off);
 }
 
@@ -1686,7 +1658,6 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
   int max_p = 1;
   for (int i = 0; i < n; ++i) max_p = std::max(max_p, d[i].terms);
   P.steps.assign(max_p - 1, {});
-  P.amax.assign(n, 0.f);
   // two passes: count tables, then lay out tables followed by buffers
   for (int pass = 0; pass < 2; ++pass) {
     Arena A;
@@ -1694,7 +1665,6 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
       P.off_items = A.take(sizeof(ExpItem) * P.items.size());
       P.off_pairs = A.take(sizeof(GemmPair) * P.pairs.size());
       P.off_scatter = A.take(sizeof(TapItem) * P.scatter.size());
-      P.off_amax = A.take(sizeof(float) * P.amax.size());
       P.off_steps.resize(P.steps.size());
       for (size_t k = 0; k < P.steps.size(); ++k) P.off_steps[k] = A.take(GemmList::bound(P.steps[k].size()));
       P.table_bytes = align_up(A.off);
@@ -1710,7 +1680,7 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
       const orth_conv_exp_desc& L = d[li];
       const int c = L.channels, k = L.k, p = L.terms, S = p * (k - 1) + 1;
       const int64_t cc = (int64_t)c * c;
-      // taps as half pieces, rows padded to whole k-steps with zeros: those
+      // taps with rows padded to whole k-steps with zeros: those
       // of L (the first power) and of the powers that a product reads.  The
       // fp32 L is read only until lt is written.
       const int cp = (int)round_up(c, 32);
@@ -1719,13 +1689,11 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
       float* acc = fbuf((int64_t)S * S * cc);
       float* lt = p > 1 ? fbuf((int64_t)k * k * ccp) : nullptr;
       float* q[2] = {p > 2 ? fbuf((int64_t)Sq * Sq * ccp) : nullptr, fbuf((int64_t)Sq * Sq * ccp)};
-      float* amax = reinterpret_cast<float*>(dev(P.off_amax)) + li;
       ExpItem e{};
       e.in = L.kernel;
       e.a = q[1];
       e.p0 = lt;
       e.ld_p = cp;
-      e.amax = amax;
       e.out = acc;
       e.c = c;
       e.k = k;
@@ -1758,8 +1726,6 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
             g.M = g.N = c;
             g.C = j < p ? cur + (int64_t)(y * sj + x) * ccp : nullptr;   // (nothing reads the last power)
             g.ldc = cp;
-            g.trans = GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT | gemm_out_exp(0);
-            g.src = amax;
             g.dst2 = acc + (int64_t)((y + off) * S + x + off) * cc;
             g.ld2 = c;
             g.beta = -1.f / j;
@@ -1772,7 +1738,6 @@ void build_conv_exp_plan(const orth_conv_exp_desc* d, int32_t n, int32_t dtype, 
     }
     P.total_bytes = align_up(A.off);
   }
-  for (auto& g : P.steps) g.run = ranged_run(true, 0, GEMM_PRE_BOTH);
   (void)dtype;
 }
 }  // namespace
@@ -1811,7 +1776,6 @@ struct VjpPlan {
   // fp32 products: a slot per matrix for the largest upstream gradient, zero
   // when the call starts
   bool f32 = false;
-  bool pieces = false;   // fp32 products: transposed iterates, E and S' stored as half pieces
   std::vector<float> gmax;
   size_t off_gmax = 0;
   size_t table_bytes = 0, total_bytes = 0;
@@ -1993,11 +1957,7 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
     }
   }
 
-  // fp32 products: tile edges and pieces (the gradient iterate is scaled to
-  // a largest value of 1 to 2, exponent 0: half's range leaves its growth
-  // over the steps a factor of 2^15)
-  const bool two_pieces = o->prescale != ORTH_PRESCALE_NONE;
-  const int x_exp = two_pieces ? kIterExp : 0;
+  // fp32 products: tile edges
   int64_t g128 = 0, u128 = 0;
   for (int i = 0; i < n; ++i)
     if (P.bucket[i] == V_F32) {
@@ -2005,11 +1965,8 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
       g128 += tn * (tn + 1) / 2;
       u128 += tiles_of(P.mats[i].Mp, 128) * tn;
     }
-  P.f_gram.run = P.b_s[0].run = P.b_s[1].run = ranged_run(two_pieces, g128, GEMM_PRE_BOTH);
-  P.f_upd.run = P.b_upd[0].run = P.b_upd[1].run = ranged_run(two_pieces, u128, GEMM_PRE_RIGHT);
-  P.pieces = two_pieces;
-  const int32_t pre_both = two_pieces ? GEMM_PRE_A | GEMM_PRE_B | GEMM_PRE_OUT : 0;
-  const int32_t pre_right = two_pieces ? GEMM_PRE_B | GEMM_PRE_OUT : 0;
+  P.f_gram.run.tile = P.b_s[0].run.tile = P.b_s[1].run.tile = gemm_tile_edge(g128);
+  P.f_upd.run.tile = P.b_upd[0].run.tile = P.b_upd[1].run.tile = gemm_tile_edge(u128);
   P.f32 = n_fu > 0;
 
   Arena A;
@@ -2141,8 +2098,6 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.ti = a;
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
-        g.exps = gemm_exps(x_exp, x_exp);
-        g.trans = pre_both | gemm_out_exp(x_exp);
         g.epi = EPI_GRAM_E;
         g.mirror = a != b;
         P.f_gram.push_back(g);
@@ -2166,8 +2121,6 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.ti = a;
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
-          h.exps = gemm_exps(x_exp, 0, 0, x_exp);
-          h.trans = pre_both;
           h.epi = EPI_NEG;
           h.mirror = a != b;
           P.b_s[par].push_back(h);
@@ -2197,8 +2150,6 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
         g.ti = a;
         g.tj = b;
         g.a_dtype = g.b_dtype = ORTH_F32;
-        g.exps = gemm_exps(x_exp, x_exp);
-        g.trans = pre_right | gemm_out_exp(x_exp);
         g.epi = EPI_UPDATE;
         g.beta = o->beta;
         P.f_upd.push_back(g);
@@ -2229,8 +2180,6 @@ void build_vjp_plan(const orth_vjp_mat* mats, int32_t n, const orth_bjorck_opts*
           h.ti = a;
           h.tj = b;
           h.a_dtype = h.b_dtype = ORTH_F32;
-          h.exps = gemm_exps(0, x_exp, x_exp, 0);
-          h.trans = pre_right;
           h.epi = EPI_UPDATE;
           h.beta = o->beta;
           P.b_upd[par].push_back(h);
@@ -2326,7 +2275,7 @@ int ortho_enqueue(const orth_mat* mats, int32_t n, const orth_bjorck_opts* opts,
     }
     ORTH_HIP(launch_prescale_finish(tm, nt, partials, opts->prescale, status, s));
     ORTH_HIP(launch_prescale_scale(tm, T(P.off_scale_items), (int)P.scale_items.size(), opts->in_dtype,
-                                   opts->compute, P.pieces, s));
+                                   opts->compute, s));
     if (bf16) {
       // per step: all Gram tiles, then all update tiles (large class first)
       for (int t = 0; t < iters; ++t)
@@ -2416,7 +2365,7 @@ int vjp_forward(const VjpPlan& P, unsigned char* ws, const orth_bjorck_opts* opt
   // a vector-Jacobian product leaves the cached vectors alone
   ORTH_HIP(launch_prescale_finish(tm, n, partials, opts->prescale, status, s, to_output ? 1 : 0));
   ORTH_HIP(launch_prescale_scale(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->in_dtype,
-                                 opts->compute, P.pieces, s));
+                                 opts->compute, s));
   for (int t = 0; t < T; ++t) {
     ORTH_HIP(launch_list(ws, P.off_f_gram, P.f_gram, "vjp_fwd_gram_f32", s, t));
     for (int cls = 1; cls >= 0; --cls)
@@ -2635,8 +2584,7 @@ int orth_orthogonalize_vjp_batched(const orth_vjp_mat* mats, int32_t n, const or
   float* gmax = P.f32 ? reinterpret_cast<float*>(ws + P.off_gmax) : nullptr;
   if (gmax)
     ORTH_HIP(launch_vjp_grad_max(tm, TI(P.off_partial_items), (int)P.partial_items.size(), opts->out_dtype, gmax, s));
-  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, gmax,
-                                P.pieces, s));
+  ORTH_HIP(launch_vjp_load_grad(tm, TI(P.off_scale_items), (int)P.scale_items.size(), opts->out_dtype, gmax, s));
   for (int b = 0; b < T; ++b) {
     const int t = T - 1 - b, par = b & 1;
     ORTH_HIP(launch_list(ws, P.off_b_s[par], P.b_s[par], "vjp_s_f32", s, t));
@@ -2974,7 +2922,6 @@ int orth_conv_exp_batched(const orth_conv_exp_desc* descs, int32_t n, int32_t dt
   put(img, P.off_items, P.items);
   put(img, P.off_pairs, P.pairs);
   put(img, P.off_scatter, P.scatter);
-  put(img, P.off_amax, P.amax);
   for (size_t k = 0; k < P.steps.size(); ++k) put(img, P.off_steps[k], P.steps[k]);
   rc = upload_tables(img, ws, s);
   if (rc) return rc;

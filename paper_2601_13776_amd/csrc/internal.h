@@ -106,86 +106,24 @@ __device__ inline void store8_f32(void* p, int64_t idx, int dtype, const float (
   }
 }
 
-// Two half pieces of 2^e x: h = half(2^e x), l = half(2^11 (2^e x - h)),
-// together 22 bits and a sign.  split2_f16 makes those of two values (h of
-// both in o[0], l in o[1]).  A matrix stored as pieces keeps the layout of
-// its fp32 form: each run of 8 values (32 bytes, starting at a multiple of
-// 8) holds the eight h, then the eight l.  A run with a value that half
-// cannot hold (an iteration that diverges, a poor estimate of sigma, NaN)
-// holds the fp32 values instead, high 16 bits in place of h, low 16 in place
-// of l, but for the first: 26 bits of it (sign, exponent, 17 bits of the
-// fraction) around an h that is a NaN.  Products of it are then NaN, so that
-// every tile which meets the run is computed again, on fp32 MFMA with
-// load_piece.
-typedef _Float16 orth_f16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t cvt2_f16(float a, float b) {
-  // (written out: left to itself the compiler folds a multiplication before
-  // it into v_fma_mixlo_f16, which takes twice the cycles of the
-  // multiplication and half a packed conversion)
-  uint32_t h;
-  asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(h) : "v"(a), "v"(b));
-  return h;
+// Three bfloat16 pieces of an fp32 value, x = h + m + l (each the rounding of
+// what the ones before leave: 8 + 8 + 8 bits, exact down to 2^-110; smaller
+// values keep 2^-134 absolute, the end of bfloat16's range).  split2_bf16
+// makes those of two values, a's in the low halves.
+typedef float orth_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 orth_bf16x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t cvt2_bf16(float a, float b) {
+  const orth_f32x2 v{a, b};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, orth_bf16x2));
 }
-__device__ __forceinline__ void split2_f16(float a, float b, float s, uint32_t& h2, uint32_t& l2) {
-  h2 = cvt2_f16(a * s, b * s);
-  const orth_f16x2 h = __builtin_bit_cast(orth_f16x2, h2);
-  l2 = cvt2_f16(fmaf(a, s, -(float)h.x) * 2048.f, fmaf(b, s, -(float)h.y) * 2048.f);
-}
-__device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
-__device__ __forceinline__ void store_pieces8(float* run, const float (&v)[8], float s) {
-  uint32_t h[4], l[4];
-  bool fits = true;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    split2_f16(v[2 * i], v[2 * i + 1], s, h[i], l[i]);
-    fits &= fabsf(v[2 * i]) * s <= 65504.f && fabsf(v[2 * i + 1]) * s <= 65504.f;
-  }
-  if (__builtin_expect(!fits, 0)) {
-    uint32_t first = __float_as_uint(v[0]);
-    first = v[0] != v[0] ? 0x7fc00000u : (first & 0x7f800000u) == 0x7f800000u ? first : first + 32;
-    h[0] = (first >> 16 & 0x8000u) | 0x7e00u | (first >> 22 & 0x1ffu);
-    l[0] = first >> 6 & 0xffffu;
-    for (int i = 1; i < 8; ++i) {
-      const uint32_t b = __float_as_uint(v[i]), at = 16 * (i & 1);
-      h[i >> 1] = at ? h[i >> 1] | (b & 0xffff0000u) : b >> 16;
-      l[i >> 1] = at ? l[i >> 1] | b << 16 : b & 0xffffu;
-    }
-  }
-  gst_u32x4(run, make_uint4(h[0], h[1], h[2], h[3]));
-  gst_u32x4(run + 4, make_uint4(l[0], l[1], l[2], l[3]));
-}
-// value k of a row stored as pieces, scaled back by `inv` = 2^-e
-__device__ __forceinline__ float load_piece(const void* row, int64_t k, float inv) {
-  const uint16_t* run = static_cast<const uint16_t*>(row) + (k >> 3) * 16;
-  const uint32_t h = gld_u16(run, k & 7), l = gld_u16(run, 8 + (k & 7)), h0 = gld_u16(run, 0);
-  if ((h0 & 0x7e00u) == 0x7e00u)
-    return __uint_as_float(k & 7 ? h << 16 | l : (h & 0x8000u) << 16 | (h & 0x1ffu) << 22 | l << 6);
-  return fmaf((float)__builtin_bit_cast(_Float16, (uint16_t)l), 1.f / 2048.f,
-              (float)__builtin_bit_cast(_Float16, (uint16_t)h)) * inv;
+__device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint32_t& m, uint32_t& l) {
+  h = cvt2_bf16(a, b);
+  const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
+  m = cvt2_bf16(ra, rb);
+  l = cvt2_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
 }
 
-// Exponent of the iterates and E as half pieces.  Iterates are scaled
-// to at most 1 (Frobenius) or to a largest singular value below sqrt(3)
-// where the iteration converges (spectral), so 2^8 times their values stay
-// far below half's 65504 (fp32 runs hold those of a diverging one), and values down to 2^-22 (4096^2 matrices start
-// at about 2^-12) keep 22 bits; smaller ones keep 2^-44 absolute.  Gradient
-// iterates start at 1 to 2 (exponent 0).
-constexpr int kIterExp = 8;
-// Exponent of the exponential map's Ahat and its powers over their
-// factorials: a poor estimate of sigma makes them large, and what they add
-// to I + ... needs no more than 2^-36 absolute.
-constexpr int kExpExp = 0;
-// The conv exponential's L has any size: its powers over their factorials
-// are stored as pieces of 2^-g times their values, with max |L| in [16, 32)
-// after scaling, so that powers may grow 2^11 times (e^9 over a few terms)
-// before runs become fp32, and what a power loses is below 2^-39 max |L|.
-__host__ __device__ inline int series_exp(float amax) {
-  if (!(amax > 0.f) || !(amax <= 3.402823466e38f)) return 0;
-  uint32_t u;
-  __builtin_memcpy(&u, &amax, 4);
-  const int e = (int)(u >> 23) - 127 - 4;
-  return e < -100 ? -100 : e > 100 ? 100 : e;
-}
+__device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // ---------------------------------------------------------------------------
 // Björck batch descriptors (device-resident tables built by the host).
@@ -306,8 +244,7 @@ enum GemmEpi : int32_t {
   EPI_UPDATE = 2,    // v = src[i][j] + beta acc; C[i][j] = v; dst2[j][i] = v if dst2
   EPI_MAXDEV = 3,    // red[0] = max(red[0], |delta_ij - acc|)
   EPI_NEG = 4,       // C[i][j] = -acc  (and C[j][i] if mirror)
-  EPI_SERIES = 5     // v = beta acc; C[i][j] = v (half pieces); dst2[i][j] += v (ld2).  With
-                     //   src (see series_exp): v = beta 2^g acc, dst2 += 2^g v
+  EPI_SERIES = 5     // v = beta acc; C[i][j] = v if C (zeros in columns N .. ldc); dst2[i][j] += v (ld2)
 };
 
 // A further operand pair of a GEMM item (same storage dtypes as the item's
@@ -337,15 +274,13 @@ struct GemmItem {
   int32_t ti, tj;
   int32_t a_dtype, b_dtype;  // storage of A and A2, of B and B2
   int32_t trans;             // GEMM_*_TRANS bits: stored [K][M], else row-major [M][K]
-  // GEMM_F16X2: the operands enter as 2^e times their values, e byte by byte
-  // (gemm_exps; further pairs as the first, both pairs with the same sum)
-  int32_t exps;
   int32_t epi;
   int32_t mirror;
   float beta;
   int32_t c_dtype;           // EPI_STORE: storage of C
   int32_t pair_base;         // further operand pairs: the launch's pair table
   int32_t pair_count;        //   [pair_base, pair_base + pair_count)
+  int32_t pad;
 };
 
 // One square output tile (the list's edge) of a GemmItem's product (the
@@ -357,36 +292,12 @@ struct GemmTile {
   int32_t pad;
 };
 
-// How a list's fp32 values enter the 16-bit matrix cores (gemm_f32.hip), and
-// how its operands are stored; a list's tiles are ordered by the latter.
-enum GemmSplit : int32_t { GEMM_BF16X3 = 0, GEMM_F16X2 = 1 };
-// GEMM_PRE_*: stored as half pieces already (row-major; see store_pieces8):
-// the A operands, the B operands, the result (dst2 of an update; its
-// exponent in gemm_out_exp).
-enum : int32_t {
-  GEMM_A_TRANS = 1,
-  GEMM_B_TRANS = 2,
-  GEMM_A2_TRANS = 4,
-  GEMM_B2_TRANS = 8,
-  GEMM_ANY_TRANS = 15,
-  GEMM_PRE_A = 16,
-  GEMM_PRE_B = 32,
-  GEMM_PRE_OUT = 64
-};
-__host__ __device__ inline int32_t gemm_out_exp(int e) { return (e & 255) << 8; }
-inline int32_t gemm_exps(int a, int b, int a2 = 0, int b2 = 0) {
-  return (int32_t)((uint32_t)(a & 255) | (uint32_t)(b & 255) << 8 | (uint32_t)(a2 & 255) << 16 |
-                   (uint32_t)(b2 & 255) << 24);
-}
+enum : int32_t { GEMM_A_TRANS = 1, GEMM_B_TRANS = 2, GEMM_A2_TRANS = 4, GEMM_B2_TRANS = 8 };
+// How a list's operands are stored; its tiles are ordered by it.
 enum GemmMode : int32_t { GEMM_ROWS = 0, GEMM_KMAJOR = 1, GEMM_ANY = 2 };
-// Which operands of a two-piece list are stored as pieces: none, B (every
-// item an update), A and B (Gram, S' and series items).
-enum GemmPre : int32_t { GEMM_PRE_NONE = 0, GEMM_PRE_RIGHT = 1, GEMM_PRE_BOTH = 2 };
 struct GemmRun {
-  int32_t split;
   int32_t tile;              // tile edge: 64 or 128
   int32_t n[3];              // tiles of each GemmMode, in this order
-  int32_t pre;
 };
 
 // Compose (AOC) descriptors: one entry per (layer, group).
@@ -481,9 +392,8 @@ hipError_t launch_prescale_partial(const TiledMat* mats, const TileItem* items, 
 // product's recomputation); matrices with sb record ||W||_F and the scale
 hipError_t launch_prescale_finish(const TiledMat* mats, int n_mats, const double* partials,
                                   int prescale, int32_t* status, hipStream_t s, int write_u = 1);
-// pieces: the transposed iterate of fp32 products is stored as half pieces
 hipError_t launch_prescale_scale(const TiledMat* mats, const TileItem* items, int n_items,
-                                 int in_dtype, int compute, int pieces, hipStream_t s);
+                                 int in_dtype, int compute, hipStream_t s);
 hipError_t launch_writeout(const TiledMat* mats, const TileItem* items, int n_items,
                            int master_index, int out_dtype, hipStream_t s);
 hipError_t launch_bf16_tiles(int big, const TiledMat* mats, const TileItem* items, int n_items, float beta,
@@ -496,7 +406,7 @@ hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const G
 hipError_t launch_vjp_grad_max(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype, float* gmax,
                                hipStream_t s);
 hipError_t launch_vjp_load_grad(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype,
-                                const float* gmax, int pieces, hipStream_t s);
+                                const float* gmax, hipStream_t s);
 hipError_t launch_vjp_dot_partial(const TiledMat* mats, const TileItem* items, int n_items, int in_dtype,
                                   double* partials, hipStream_t s);
 hipError_t launch_vjp_dot_finish(const TiledMat* mats, int n_mats, const double* partials, hipStream_t s);
@@ -520,9 +430,8 @@ struct ExpItem {
   float* a;                  // exp map: A = W - W^T (C x C); conv: L taps (k x k grid)
   float* out;                // the fp32 series accumulator (C x C, or S x S taps)
   float* p0;                 // first power (Ahat; conv: the L taps, k x k matrices of
-                             //   c x ld_p) as half pieces, row stride ld_p, zero past c
+                             //   c x ld_p; nullptr: not needed), row stride ld_p, zero past c
   int64_t ld_p;
-  float* amax;               // conv: receives max |L| (zero before)
   const float* inv;          // exp map: 1 / sigma of A (from the spectral pre-scaling kernels)
   int64_t ld_in;
   int32_t c;                 // C, or channels c

@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void prescale_finish_kernel(const TiledMat* __
 
 __global__ __launch_bounds__(256) void prescale_scale_kernel(const TiledMat* __restrict__ mats,
                                                              const TileItem* __restrict__ items,
-                                                             int in_dtype, int compute, int pieces) {
+                                                             int in_dtype, int compute) {
   __shared__ float tile[TB][TB + 1];
   const TileItem it = items[blockIdx.x];
   const TiledMat& d = mats[it.mat];
@@ -165,18 +165,8 @@ __global__ __launch_bounds__(256) void prescale_scale_kernel(const TiledMat* __r
     // bf16 products: the bf16 copy; fp32 products: the transposed iterate
     // xt[(C + a)][(R + b)] = tile[b][a] (each only where the plan has one)
     if (compute == ORTH_COMPUTE_BF16 && d.xc[0]) gst_u16(d.xc[0], off, f32_to_bf16(v));
-    if (compute != ORTH_COMPUTE_BF16 && d.xt && !pieces)
+    if (compute != ORTH_COMPUTE_BF16 && d.xt)
       gst_f32(d.xt, (int64_t)(C + a) * d.Mp + R + b, tile[b][a]);
-  }
-  if (pieces && compute != ORTH_COMPUTE_BF16 && d.xt) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int u = threadIdx.x + 256 * h, a = u >> 3, b = (u & 7) * 8;
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = tile[b + i][a];
-      store_pieces8(static_cast<float*>(d.xt) + (int64_t)(C + a) * d.Mp + R + b, v, pow2f(kIterExp));
-    }
   }
 }
 
@@ -249,12 +239,11 @@ hipError_t launch_prescale_finish(const TiledMat* mats, int n_mats, const double
   return e;
 }
 
-hipError_t launch_prescale_scale(const TiledMat* mats, const TileItem* items, int n_items,
-                                 int in_dtype, int compute, int pieces, hipStream_t s) {
+hipError_t launch_prescale_scale(const TiledMat* mats, const TileItem* items, int n_items, int in_dtype,
+                                 int compute, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   timing_begin("prescale_scale", s);
-  hipLaunchKernelGGL(prescale_scale_kernel, dim3(n_items), dim3(256), 0, s, mats, items, in_dtype, compute,
-                     pieces);
+  hipLaunchKernelGGL(prescale_scale_kernel, dim3(n_items), dim3(256), 0, s, mats, items, in_dtype, compute);
   hipError_t e = hipGetLastError();
   timing_end("prescale_scale", s);
   return e;

@@ -1,9 +1,10 @@
 // Layout and pre-scaling kernels of the Björck vector-Jacobian product.
 //
 //   grad_max    : largest |dL/d(output)| of every matrix with fp32 products
-//                 (those products take the gradient iterate as half pieces:
-//                 it is scaled by the power of two that brings that value
-//                 to 1 to 2, and the result back)
+//                 (the gradient iterate is scaled by the power of two that
+//                 brings that value to 1 to 2, and the result back: the low
+//                 pieces of its products then stay far from the end of
+//                 fp32's range whatever the loss is scaled by)
 //   load_grad   : dL/d(output) from the caller's layout and dtype into the
 //                 tall, zero-padded fp32 gradient iterate (plus its bf16
 //                 copy for bf16 products)
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(256) void vjp_grad_max_kernel(const TiledMat* __res
 
 __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __restrict__ mats,
                                                             const TileItem* __restrict__ items, int gout_dtype,
-                                                            const float* __restrict__ gmax, int pieces) {
+                                                            const float* __restrict__ gmax) {
   __shared__ float tile[TB][TB + 1];
   const TileItem it = items[blockIdx.x];
   const TiledMat& d = mats[it.mat];
@@ -138,17 +139,7 @@ __global__ __launch_bounds__(256) void vjp_load_grad_kernel(const TiledMat* __re
     if (yc) gst_u16(yc, off, f32_to_bf16(tile[a][b]));
     // fp32 products: the transpose too, Np x Mp (consecutive threads along
     // a, so its rows are written coalesced)
-    if (yt && !pieces) gst_f32(yt, (int64_t)(C + a) * d.Mp + R + b, tile[b][a]);
-  }
-  if (yt && pieces) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int u = threadIdx.x + 256 * h, a = u >> 3, b = (u & 7) * 8;
-      float v[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = tile[b + i][a];
-      store_pieces8(yt + (int64_t)(C + a) * d.Mp + R + b, v, 1.f);
-    }
+    if (yt) gst_f32(yt, (int64_t)(C + a) * d.Mp + R + b, tile[b][a]);
   }
 }
 
@@ -296,11 +287,10 @@ hipError_t launch_vjp_grad_max(const TiledMat* mats, const TileItem* items, int 
 }
 
 hipError_t launch_vjp_load_grad(const TiledMat* mats, const TileItem* items, int n_items, int gout_dtype,
-                                const float* gmax, int pieces, hipStream_t s) {
+                                const float* gmax, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   timing_begin("vjp_load_grad", s);
-  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax,
-                     pieces);
+  hipLaunchKernelGGL(vjp_load_grad_kernel, dim3(n_items), dim3(256), 0, s, mats, items, gout_dtype, gmax);
   hipError_t e = hipGetLastError();
   timing_end("vjp_load_grad", s);
   return e;

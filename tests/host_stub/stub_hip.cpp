@@ -303,7 +303,7 @@ hipError_t launch_prescale_finish(const TiledMat* mats, int n, const double*, in
   table(mats, n, "launch_prescale_finish");
   return launched();
 }
-hipError_t launch_prescale_scale(const TiledMat*, const TileItem* items, int n, int, int, int, hipStream_t) {
+hipError_t launch_prescale_scale(const TiledMat*, const TileItem* items, int n, int, int, hipStream_t) {
   table(items, n, "launch_prescale_scale");
   return launched();
 }
@@ -320,8 +320,6 @@ hipError_t launch_gemm_f32(const GemmItem* items, const GemmTile* tiles, const G
   if (run.tile != 64 && run.tile != 128) violation("tile edge", name, 0, (size_t)run.tile);
   for (int k : run.n)
     if (k < 0) violation("tile count out of range", name, 0, (size_t)k);
-  if (run.split == GEMM_F16X2 && run.n[GEMM_KMAJOR] + run.n[GEMM_ANY] > 0)
-    violation("two pieces planned for other than row-major products", name, 0, 0);
   const int n_tiles = run.n[0] + run.n[1] + run.n[2];
   std::copy(run.n, run.n + 3, t_gemm_tiles);
   if (n_tiles > 0) table(items, 1, name);
@@ -333,8 +331,7 @@ hipError_t launch_vjp_grad_max(const TiledMat*, const TileItem* items, int n, in
   table(gmax, 1, "launch_vjp_grad_max (slots)");
   return launched();
 }
-hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, const float*, int,
-                                hipStream_t) {
+hipError_t launch_vjp_load_grad(const TiledMat*, const TileItem* items, int n, int, const float*, hipStream_t) {
   table(items, n, "launch_vjp_load_grad");
   return launched();
 }

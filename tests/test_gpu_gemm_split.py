@@ -1,6 +1,8 @@
 """fp32 products on 16-bit matrix cores: the sizes where the tiles, the
-K-steps and the choice of tile edge can go wrong, the values that the split
-cannot carry (infinities, overflow), and the scaling of gradients."""
+K-steps and the choice of tile edge can go wrong, inputs whose parts differ
+by many powers of two (every part keeps fp32's relative accuracy), the
+values that the split cannot carry (infinities, overflow), and the scaling
+of gradients."""
 
 import numpy as np
 import pytest
@@ -61,7 +63,6 @@ def test_gram_of_long_strides(rows, cols, ld):
 
 
 # light rows keep their own relative accuracy beside rows 2^10 times larger
-# (the half pieces' range)
 def test_row_scales():
     m = _rand(3, 192, 128)
     m[::7] *= 1024.0
@@ -69,6 +70,60 @@ def test_row_scales():
     ref = bjorck.bjorck(m.astype(np.float64), 5)
     light = np.arange(192) % 7 != 0
     assert checks.relative_difference(got[light], ref[light]) <= TOL
+
+
+# and at any ratio, before and at convergence (a light column grows by at
+# most 3/2 a step, so 2^-30 needs more than 51 of them)
+@pytest.mark.parametrize("prescale", ["frobenius", "spectral"])
+@pytest.mark.parametrize("exp", [-20, -24, -30])
+def test_light_rows_and_columns(exp, prescale):
+    def run(m, iters):
+        u = _rand(14, min(m.shape))
+        kw = dict(u=torch.from_numpy(u.copy()).to(DEV), power_iters=4) if prescale == "spectral" else {}
+        got = _run([m], iters, prescale=prescale, **kw)[0]
+        m64 = m.astype(np.float64)
+        return got, (spectral.bjorck_spectral(m64, u.astype(np.float64), iters, 4)[0] if kw else
+                     bjorck.bjorck(m64, iters))
+    for shape in [(192, 128), (513, 256), (130, 300)]:
+        m = _rand(13, *shape)
+        m[::7] *= np.float32(2.0 ** exp)
+        got, ref = run(m, 12)
+        light = np.arange(shape[0]) % 7 == 0
+        for rows in (light, ~light):
+            assert checks.relative_difference(got[rows], ref[rows]) <= TOL, (shape, "rows")
+        m = _rand(15, *shape)
+        m[:, ::7] *= np.float32(2.0 ** exp)
+        light = np.arange(shape[1]) % 7 == 0
+        for iters in (12, 70):
+            got, ref = run(m, iters)
+            for cols in (light, ~light):
+                assert checks.relative_difference(got[:, cols], ref[:, cols]) <= TOL, (shape, "columns", iters)
+
+
+# gradients of two uncoupled blocks that differ by 2^exp (the cached vector
+# lies in the first one, whose leading singular value sets sigma): each
+# block's gradient keeps its own relative accuracy
+@pytest.mark.parametrize("saved", [False, True])
+@pytest.mark.parametrize("exp", [-20, -30])
+def test_light_gradient_block(exp, saved):
+    m, g = np.zeros((192, 128), np.float32), np.zeros((192, 128), np.float32)
+    u = np.zeros(128, np.float32)
+    a, b = _rand(40, 96), _rand(41, 64)
+    m[:96, :64] = _rand(42, 96, 64) + 60.0 * np.outer(a / np.linalg.norm(a), b / np.linalg.norm(b))
+    m[96:, 64:] = _rand(43, 96, 64)
+    u[:64] = _rand(44, 64)
+    g[:96, :64] = _rand(45, 96, 64)
+    g[96:, 64:] = _rand(46, 96, 64) * np.float32(2.0 ** exp)
+    w, go, ut = (torch.from_numpy(v).to(DEV) for v in (m, g, u.copy()))
+    out = torch.empty_like(w)
+    kw = dict(prescale="spectral", power_iters=2)
+    ws = orth.orth_orthogonalize_save_batched([w], [torch.empty_like(w)], 6, u=ut, **kw) if saved else None
+    orth.orth_orthogonalize_vjp_batched([w], [go], [out], 6, u=None if saved else ut, workspace=ws, saved=saved, **kw)
+    got = out.cpu().numpy().astype(np.float64)
+    m64, g64 = m.astype(np.float64), g.astype(np.float64)
+    ref = spectral.bjorck_spectral_vjp(m64, u.astype(np.float64), g64, 6, 2)
+    for rows, cols in ((slice(0, 96), slice(0, 64)), (slice(96, 192), slice(64, 128))):
+        assert checks.relative_difference(got[rows, cols], ref[rows, cols]) <= TOL
 
 
 # an infinity comes out as fp32 arithmetic has it, and a value that rounds to
@@ -138,11 +193,9 @@ def test_gradient_nonfinite():
         assert torch.equal(out[1], ref[1])
 
 
-# values that half cannot hold: the estimate of sigma misses a heavy block
-# (the cached vector has no part in it), so the iterates of a few steps, E
-# and the powers leave the half pieces' range.  Such runs are stored as fp32
-# values, the first of each 8 with 18 bits (2^-19 relative); a step cubes the
-# iterate, so k steps carry 3^k 2^-19 / sqrt(8) of it.
+# iterates and powers that grow: the estimate of sigma misses a heavy block
+# (the cached vector has no part in it), so the iterates of a few steps and
+# the powers leave the range that a good estimate gives them
 def _heavy(c, heavy):
     m = _rand(20, c, c)
     m[:, -heavy:] = 0.0
@@ -159,7 +212,7 @@ def test_diverging_spectral(c, heavy, iters):
     got = _run([m], iters, prescale="spectral", u=torch.from_numpy(u.copy()).to(DEV))[0]
     ref, _, _ = spectral.bjorck_spectral(m.astype(np.float64), u.astype(np.float64), iters, 1)
     assert np.abs(ref).max() > 200
-    assert checks.relative_difference(got, ref) <= TOL + 3 ** iters * 2.0 ** -20.5
+    assert checks.relative_difference(got, ref) <= TOL
 
 
 @pytest.mark.parametrize("c,heavy,terms", [(512, 2, 8), (450, 2, 9), (2000, 2, 12)])
@@ -170,13 +223,34 @@ def test_exp_map_poor_sigma(c, heavy, terms):
     orth.orth_exp_map_batched([w], [out], terms, torch.from_numpy(u.copy()).to(DEV), 1)
     ref, _ = expo.exp_map(m.astype(np.float64), terms, u.astype(np.float64))
     assert np.abs(ref).max() > 65504
-    assert checks.relative_difference(out.cpu().numpy().astype(np.float64), ref) <= TOL + terms * 2.0 ** -20.5
+    assert checks.relative_difference(out.cpu().numpy().astype(np.float64), ref) <= TOL
+
+
+# light channels of the exponentials: rows and columns 2^-30 times the
+# others' keep their own relative accuracy off the diagonal
+@pytest.mark.parametrize("c", [96, 200])
+def test_exp_light_channels(c):
+    light = np.arange(c) % 5 == 0
+    f = np.where(light, np.float32(2.0 ** -30), np.float32(1.0))
+    m, u = _rand(50, c, c) * f[:, None] * f, _rand(51, c) * f
+    out = torch.empty(c, c, device=DEV)
+    orth.orth_exp_map_batched([torch.from_numpy(m).to(DEV)], [out], 8, torch.from_numpy(u.copy()).to(DEV), 2)
+    ref, _ = expo.exp_map(m.astype(np.float64), 8, u.astype(np.float64), 2)
+    got = out.cpu().numpy().astype(np.float64)
+    assert checks.relative_difference(got[~light][:, light], ref[~light][:, light]) <= TOL
+    assert checks.relative_difference(got[light][:, ~light], ref[light][:, ~light]) <= TOL
+    kern = _rand(52, c, c, 3, 3) * (f[:, None] * f)[:, :, None, None]
+    co = torch.empty(c, c, 7, 7, device=DEV)
+    orth.orth_conv_exp_batched([dict(kernel=torch.from_numpy(kern).to(DEV), out=co, terms=3, scale=0.02)])
+    ref = expo.conv_exp(kern.astype(np.float64), 3, float(np.float32(0.02)))
+    got = co.cpu().numpy().astype(np.float64)
+    assert checks.relative_difference(got[~light][:, light], ref[~light][:, light]) <= TOL
+    assert checks.relative_difference(got[light][:, ~light], ref[light][:, ~light]) <= TOL
 
 
 # conv exponentials: channel counts at the edges of the padded rows and
 # tiles (the last one fills every compute unit with 128-tiles), series of 2
-# and 3 terms, kernels of any size; of the last three scales the powers
-# outgrow the half pieces after the first step, at once, and never
+# and 3 terms, kernels of any size
 @pytest.mark.parametrize("c,k,terms,scale", [(31, 3, 3, 0.05), (33, 5, 4, 0.1), (65, 3, 2, 0.02), (96, 1, 5, 0.05),
                                              (512, 3, 3, 0.004), (40, 3, 4, 40.0), (16, 5, 3, 1e8),
                                              (24, 3, 4, 1e-9)])
@@ -187,8 +261,7 @@ def test_conv_exp_pieces(c, k, terms, scale):
     orth.orth_conv_exp_batched([dict(kernel=torch.from_numpy(kern).to(DEV), out=out, terms=terms, scale=scale)])
     got = out.cpu().numpy().astype(np.float64)
     ref = expo.conv_exp(kern.astype(np.float64), terms, float(np.float32(scale)))
-    tol = TOL + (terms * 2.0 ** -20.5 if scale > 1 else 0.0)
-    assert checks.relative_difference(got, ref) <= tol
+    assert checks.relative_difference(got, ref) <= TOL
     if scale < 1e-6:   # the kernel itself, beside the identity
         eye = np.zeros_like(ref)
         eye[np.arange(c), np.arange(c), S // 2, S // 2] = 1.0
