@@ -237,8 +237,8 @@ __global__ __launch_bounds__(256) void conv_apply_kernel(ApplyGeom G, const void
 // fp32 accumulation, the leading product and the corrections in an
 // accumulator each (a kernel stored in bf16 is its own leading piece: three
 // products).  The relative error against 64 bits is about a third of fp32
-// MFMA's.  A wave with a non-finite result computes its block again with
-// fp32 MFMA (an infinity splits into inf - inf).
+// MFMA's.  A block with a result that the split cannot give (split_failed) is
+// computed again with fp32 MFMA.
 //
 // Work: a tile is 64 output channels x 128 pixels of a grid (4 waves of 32 x
 // 64); the reduction runs in chunks of CB = 8 G8 channels.  Per chunk, every
@@ -297,37 +297,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
-
-// A wave's 32 x 32 block with fp32 MFMA: this lane's channel `row` of the
-// group (as MFMA row) and output pixel (as column), the original formula.
-template <bool TR>
-__device__ __forceinline__ f32x16 conv_block_f32(const ApplyGeom& G, const void* kern, const float* x, int grp,
-                                                 int row, bool pix_ok, int b, int p, int q) {
-  f32x16 acc = {};
-  const int half = (threadIdx.x >> 5) & 1, kk2 = G.k * G.k;
-  const int64_t cplane = TR ? (int64_t)G.Ho * G.Wo : (int64_t)G.H * G.W;
-  const float* xb = x + ((int64_t)b * (TR ? G.cout : G.cin) + (int64_t)grp * (TR ? G.og : G.c)) * cplane;
-  for (int k0 = 0; k0 < G.red; k0 += 2) {
-    const int kk = k0 + half;
-    float av = 0.f, bv = 0.f;
-    if (kk < G.red) {
-      const int ch = kk / kk2, tap = kk - ch * kk2, a = tap / G.k, e = tap - a * G.k;
-      if (row < G.rows)
-        av = load_as_f32(kern, TR ? ((int64_t)(grp * G.og + ch) * G.c + row) * kk2 + tap
-                                  : (int64_t)(grp * G.og + row) * G.red + kk, G.kdtype);
-      if (pix_ok) {
-        const int r = pmod(TR ? p + G.pl - G.d * a : G.s * p + G.d * a - G.pl, G.H);
-        const int c = pmod(TR ? q + G.pl - G.d * e : G.s * q + G.d * e - G.pl, G.W);
-        if (!TR)
-          bv = gld_f32(xb, ch * cplane + (int64_t)r * G.W + c);
-        else if (r % G.s == 0 && c % G.s == 0)
-          bv = gld_f32(xb, ch * cplane + (int64_t)(r / G.s) * G.Wo + c / G.s);
-      }
-    }
-    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
-  }
-  return acc;
-}
 
 template <bool TR, int KS, int PH, bool KBF16, int PU>
 __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, StageGeom T,
@@ -586,14 +555,108 @@ __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, 
     }
   }
 
+  // the grid position of this lane's pixel in block i (PH == 4: in every block)
+  auto pixel = [&](int i) { return p0 + wn * (BN / 2) + (PH == 4 ? 0 : i * 32) + (lane & 31); };
+  uint32_t redo = 0;   // this wave's blocks that fp32 MFMA has to compute
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    bool bad = false;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      acc[0][i][r] += acc[1][i][r];
+      bad |= split_failed(acc[0][i][r]);
+    }
+    redo |= __any(bad && pixel(i) < T.pix) ? 1u << i : 0u;
+  }
+  uint32_t* const votes = reinterpret_cast<uint32_t*>(smem4);
+  __syncthreads();   // the last chunk is read
+  if (lane == 0) votes[wave] = redo;
+  __syncthreads();
+  const int redo_tile = __builtin_amdgcn_readfirstlane(votes[0] | votes[1] | votes[2] | votes[3]);
+  if (__builtin_expect(redo_tile != 0, 0)) {
+    // The tile on fp32 MFMA from fp32 values in the same places: groups of 8
+    // channels per (entry, row) (a bfloat16 kernel stays as it is) and per
+    // position; a wave's halves hold the even and the odd four channels of a
+    // group.  The blocks that asked for it take the result.
+    float* const Af = reinterpret_cast<float*>(As);
+    float* const Xf = reinterpret_cast<float*>(Xs);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) acc[1][i] = f32x16{};
+    // (its own offsets: with those of the pass above the compiler keeps whole
+    // addresses for both, 100 registers more at k = 1)
+#pragma unroll
+    for (int i = 0; i < PU; ++i) asm volatile("" : "+v"(xoff[i]));
+    load(0);
+    for (int ch0 = 0; ch0 < T.nch; ch0 += CB) {
+      __syncthreads();
+#pragma unroll
+      for (int g = 0; g < G8; ++g)
+#pragma unroll
+        for (int t = 0; t < KK; ++t) {
+          const int dst = entry(t, g) * 64 + krow;
+          const int left = T.nch - (ch0 + 8 * g + 2 * kc2);   // channels past the end are zero
+          if constexpr (KBF16) {
+            uint32_t a = (ra[g][0][t / 2] >> (t & 1 ? 16 : 0)) & 0xffffu;
+            uint32_t b = (ra[g][1][t / 2] >> (t & 1 ? 16 : 0)) & 0xffffu;
+            reinterpret_cast<uint32_t*>(As)[dst * 4 + kc2] = (left > 0 ? a : 0u) | (left > 1 ? b << 16 : 0u);
+          } else {
+            Af[dst * 8 + 2 * kc2] = left > 0 ? __uint_as_float(ra[g][0][t]) : 0.f;
+            Af[dst * 8 + 2 * kc2 + 1] = left > 1 ? __uint_as_float(ra[g][1][t]) : 0.f;
+          }
+        }
+#pragma unroll
+      for (int i = 0; i < PU; ++i) {
+        const int pos = tid + i * 256;
+        if (pos < T.npos) {
+#pragma unroll
+          for (int g = 0; g < G8; ++g)
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+              Xf[(g * T.npos + pos) * 8 + c] = ch0 + 8 * g + c < T.nch ? rx[i][g][c] : 0.f;
+        }
+      }
+      __syncthreads();
+      load(ch0 + CB < T.nch ? ch0 + CB : ch0);
+#pragma unroll
+      for (int g = 0; g < G8; ++g)
+#pragma unroll
+        for (int t = 0; t < KK; ++t) {
+          const int at = entry(t, g) * 64 + arow, a = t / KS, e = t % KS;
+          const int off = g * T.npos + (KS == 1 ? 0 : (T.rows_sep ? a : T.rt[a] - T.rmin) * T.WX + (T.ct[e] - T.cmin));
+          float fa[4];
+          if constexpr (KBF16) {
+            const uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint32_t*>(As) + at * 4 + 2 * half);
+            fa[0] = __uint_as_float(w.x << 16);
+            fa[1] = __uint_as_float(w.x & 0xffff0000u);
+            fa[2] = __uint_as_float(w.y << 16);
+            fa[3] = __uint_as_float(w.y & 0xffff0000u);
+          } else {
+            const float4 w = *reinterpret_cast<const float4*>(Af + at * 8 + 4 * half);
+            fa[0] = w.x; fa[1] = w.y; fa[2] = w.z; fa[3] = w.w;
+          }
+#pragma unroll
+          for (int i = 0; i < (PH == 4 ? 1 : NB); ++i) {
+            const float4 w = *reinterpret_cast<const float4*>(Xf + (poff[i] + off) * 8 + 4 * half);
+            const float fb[4] = {w.x, w.y, w.z, w.w};
+            f32x16& sum = acc[1][PH == 4 ? phase_of(entry(t, g) >> 1) : i];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c], fb[c], sum, 0, 0, 0);
+          }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+      if (redo >> i & 1) acc[0][i] = acc[1][i];
+  }
+
   // columns are pixels: consecutive lanes store consecutive pixels
   const int oh = TR ? G.H : G.Ho, ow = TR ? G.W : G.Wo;
   const int ych = TR ? G.cin : G.cout, chb = grp * (TR ? G.c : G.og);
   const int64_t plane = (int64_t)oh * ow;
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
-    const int64_t pn = p0 + wn * (BN / 2) + (PH == 4 ? 0 : i * 32) + (lane & 31);
-    const bool ok = pn < T.pix;
+    const int64_t pn = pixel(i);
+    if (pn >= T.pix) continue;
     const int64_t orow = pn / T.Wg;
     const int b = (int)(orow / T.Hg);
     int u = (int)(orow - (int64_t)b * T.Hg), v = (int)(pn - orow * T.Wg);
@@ -604,15 +667,6 @@ __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, 
       u = T.os * u + pfh;
       v = T.os * v + pfw;
     }
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      acc[0][i][r] += acc[1][i][r];
-      bad |= !isfinite(acc[0][i][r]);
-    }
-    if (__builtin_expect(__any(bad && ok), 0))
-      acc[0][i] = conv_block_f32<TR>(G, kern, x, grp, row0 + wm * 32 + (lane & 31), ok, ok ? b : 0, u, v);
-    if (!ok) continue;
     float* yp = y + ((int64_t)b * ych + chb) * plane + (int64_t)u * ow + v;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {

@@ -93,27 +93,6 @@ __device__ __forceinline__ PairView pair_view(const GemmItem& g, const GemmPair*
   return v;
 }
 
-// The wave's 32 x 32 block at (i0, j0) with fp32 MFMA and guarded loads: the
-// tiles whose split result is not finite.
-__device__ __forceinline__ f32x16 block_f32(const GemmItem& g, const GemmPair* extra, int64_t st, int i0,
-                                            int j0) {
-  const int lane = threadIdx.x & 63;
-  const int i = i0 + (lane & 31), j = j0 + (lane & 31);
-  f32x16 acc = {};
-  const int npairs = 2 + g.pair_count;
-  for (int pair = 0; pair < npairs; ++pair) {
-    const PairView v = pair_view(g, extra, pair, st);
-    for (int k0 = 0; k0 < v.K; k0 += 2) {
-      const int k = k0 + (lane >> 5);
-      float a = 0.f, b = 0.f;
-      if (i < g.M && k < v.K) a = load_as_f32(v.A, v.atr ? k * v.lda + i : i * v.lda + k, g.a_dtype);
-      if (j < g.N && k < v.K) b = load_as_f32(v.B, v.btr ? k * v.ldb + j : j * v.ldb + k, g.b_dtype);
-      acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
-    }
-  }
-  return acc;
-}
-
 // MODE: the operands of every tile of the launch are GEMM_ROWS all fp32 and
 // row-major ([M][K]), GEMM_KMAJOR all fp32, stored [K][M] and with M and N
 // multiples of four, GEMM_ANY fp32 or bf16 in either order.  A thread loads
@@ -226,45 +205,50 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
                         __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
     split_store(x, MODE == GEMM_KMAJOR, s, o);
   };
-  // the step at k0 of pair v, whole or not, into stage s: guarded loads
+  // this thread's values of operand o at k0 of pair v, a whole step or not
+  // (zeros past the end); returns whether they lie k-major
+  auto load_guarded = [&](const PairView& v, int k0, int o, float (&x)[8]) -> bool {
+    const char* ptr = o ? v.B : v.A;
+    const int64_t ld = o ? v.ldb : v.lda;
+    const bool tro = MODE == GEMM_KMAJOR || (MODE == GEMM_ANY && (o ? v.btr : v.atr) != 0);
+    const int dt = o ? bdt : adt, base = o ? col0 : row0, lim = o ? N : M;
+    if (k0 + BK <= v.K && dt == ORTH_F32 && (!tro || base + BM <= lim || lim % 4 == 0)) {
+      const int r = tro ? (base + tr + 4 <= lim ? base + tr : lim - 4) : (base + rr < lim ? base + rr : lim - 1);
+      const float* p = reinterpret_cast<const float*>(ptr) +
+                       (tro ? (int64_t)(k0 + tk) * ld + r : (int64_t)r * ld + k0 + rc * 8);
+      const uint4 a = gld_u32x4_a4(p), b = gld_u32x4_a4(tro ? p + ld : p + 4);
+      x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y); x[2] = __uint_as_float(a.z);
+      x[3] = __uint_as_float(a.w); x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
+      x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
+    } else if (MODE == GEMM_ANY && k0 + BK <= v.K && dt == ORTH_BF16 && !tro && vec8_ok(ptr, ld, ORTH_BF16)) {
+      load8_f32(ptr, (int64_t)(base + rr < lim ? base + rr : lim - 1) * ld + k0 + rc * 8, ORTH_BF16, x);
+    } else {
+      // (raw bits first: a conversion inside the guarded load would make
+      // every load wait for its data)
+      uint32_t w[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int r = base + (tro ? tr + (q & 3) : rr), k = k0 + (tro ? tk + (q >> 2) : rc * 8 + q);
+        w[q] = 0;
+        if (r < lim && k < v.K) {
+          const int64_t e = tro ? (int64_t)k * ld + r : (int64_t)r * ld + k;
+          w[q] = dt == ORTH_BF16 ? (uint32_t)gld_u16(ptr, e) : gld_u32(ptr, e);
+        }
+      }
+      const int sh = dt == ORTH_BF16 ? 16 : 0;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        asm volatile("" : "+v"(w[q]));
+        x[q] = __uint_as_float(w[q] << sh);
+      }
+    }
+    return tro;
+  };
   auto stage_guarded = [&](const PairView& v, int k0, int s) {
 #pragma unroll
     for (int o = 0; o < 2; ++o) {
-      const char* ptr = o ? v.B : v.A;
-      const int64_t ld = o ? v.ldb : v.lda;
-      const bool tro = MODE == GEMM_KMAJOR || (MODE == GEMM_ANY && (o ? v.btr : v.atr) != 0);
-      const int dt = o ? bdt : adt, base = o ? col0 : row0, lim = o ? N : M;
       float x[8];
-      if (MODE == GEMM_ANY && k0 + BK <= v.K && dt == ORTH_F32 && (!tro || base + BM <= lim || lim % 4 == 0)) {
-        const int r = tro ? (base + tr + 4 <= lim ? base + tr : lim - 4) : (base + rr < lim ? base + rr : lim - 1);
-        const float* p = reinterpret_cast<const float*>(ptr) +
-                         (tro ? (int64_t)(k0 + tk) * ld + r : (int64_t)r * ld + k0 + rc * 8);
-        const uint4 a = gld_u32x4_a4(p), b = gld_u32x4_a4(tro ? p + ld : p + 4);
-        x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y); x[2] = __uint_as_float(a.z);
-        x[3] = __uint_as_float(a.w); x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
-        x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
-      } else if (MODE == GEMM_ANY && k0 + BK <= v.K && dt == ORTH_BF16 && !tro && vec8_ok(ptr, ld, ORTH_BF16)) {
-        load8_f32(ptr, (int64_t)(base + rr < lim ? base + rr : lim - 1) * ld + k0 + rc * 8, ORTH_BF16, x);
-      } else {
-        // (raw bits first: a conversion inside the guarded load would make
-        // every load wait for its data)
-        uint32_t w[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const int r = base + (tro ? tr + (q & 3) : rr), k = k0 + (tro ? tk + (q >> 2) : rc * 8 + q);
-          w[q] = 0;
-          if (r < lim && k < v.K) {
-            const int64_t e = tro ? (int64_t)k * ld + r : (int64_t)r * ld + k;
-            w[q] = dt == ORTH_BF16 ? (uint32_t)gld_u16(ptr, e) : gld_u32(ptr, e);
-          }
-        }
-        const int sh = dt == ORTH_BF16 ? 16 : 0;
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          asm volatile("" : "+v"(w[q]));
-          x[q] = __uint_as_float(w[q] << sh);
-        }
-      }
+      const bool tro = load_guarded(v, k0, o, x);
       split_store(x, tro, s, o);
     }
   };
@@ -379,9 +363,10 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
       for (int r = 0; r < 16; ++r) {
         const float v = acc[0][i][j][r] + acc[1][i][j][r];
         acc[0][i][j][r] = v;
-        bad |= !isfinite(v);
+        bad |= split_failed(v);
       }
-  if (__builtin_expect(__any(bad), 0)) {
+  bool redo = __any(bad);
+  if (__builtin_expect(redo, 0)) {
     // every row of the wave's part of A starts with a NaN: so does the
     // fp32 result (a matrix that is NaN throughout)
     bool all_nan = true;
@@ -395,12 +380,58 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
         all_nan = false;
       }
     }
-    if (!__all(all_nan)) {
+    redo = !__all(all_nan);
+  }
+  // (the votes lie past what the epilogues use)
+  int* const votes = reinterpret_cast<int*>(smem) + 2 * 2 * P * BM * CH * 4 - WM * WN;
+  if (lane == 0) votes[wave] = redo;
+  __syncthreads();
+  int redo_tile = 0;
+#pragma unroll
+  for (int w = 0; w < WM * WN; ++w) redo_tile |= votes[w];
+  if (__builtin_expect(__builtin_amdgcn_readfirstlane(redo_tile) != 0, 0)) {
+    // The tile on fp32 MFMA, its operands' fp32 values through LDS, a step
+    // at a time; the waves that asked for it take the result.
+    constexpr int LD = BK + 1;
+    float* const F = reinterpret_cast<float*>(smem);   // [operand][BM rows][LD]
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NI; ++j) acc[1][i][j] = f32x16{};
+    for (int p = 0; p < npairs; ++p) {
+      const PairView v = pair_view(item, extra, p, st);
+      for (int k0 = 0; k0 < v.K; k0 += BK) {
+        float x[2][8];
+        bool tro[2];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) tro[o] = load_guarded(v, k0, o, x[o]);
+        __syncthreads();   // the votes, or the step before, are read
+#pragma unroll
+        for (int o = 0; o < 2; ++o)
+#pragma unroll
+          for (int q = 0; q < 8; ++q)
+            F[(o * BM + (tro[o] ? tr + (q & 3) : rr)) * LD + (tro[o] ? tk + (q >> 2) : rc * 8 + q)] = x[o][q];
+        __syncthreads();
+        for (int kk = 0; kk < BK; kk += 2) {
+          float fa[MI], fb[NI];
+#pragma unroll
+          for (int i = 0; i < MI; ++i) fa[i] = F[(wm * (BM / WM) + i * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
+#pragma unroll
+          for (int j = 0; j < NI; ++j) fb[j] = F[(BM + wn * (BM / WN) + j * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
+#pragma unroll
+          for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+              acc[1][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[1][i][j], 0, 0, 0);
+        }
+      }
+    }
+    __syncthreads();   // the epilogue reuses LDS
+    if (redo) {
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
-        for (int j = 0; j < NI; ++j)
-          acc[0][i][j] = block_f32(item, extra, st, row0 + wm * (BM / WM) + i * 32, col0 + wn * (BM / WN) + j * 32);
+        for (int j = 0; j < NI; ++j) acc[0][i][j] = acc[1][i][j];
     }
   }
 

@@ -123,6 +123,11 @@ __device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint3
   l = cvt2_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
 }
 
+// Whether split products cannot stand for a result of theirs: it is not
+// finite (an infinity splits into inf - inf, a value past bfloat16's largest
+// into an infinity).
+__device__ __forceinline__ bool split_failed(float v) { return !isfinite(v); }
+
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 
 // ---------------------------------------------------------------------------

@@ -85,3 +85,30 @@ def test_extreme_inputs(bad, stride, transposed):
         k64 = kern.astype(np.float32).astype(np.float64)
         ref = conv.conv_circular_adjoint(k64, ref, (h, h), stride) if transposed else conv.conv_circular(k64, ref, stride)
         assert np.allclose(got[hit].astype(np.float64), ref[hit], rtol=1e-6)
+
+
+# one infinite input at every geometry: the tiles that meet it are computed
+# again with fp32 products, and everything outside its window is what it was
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("geom,b,h,w", CASES)
+def test_nonfinite_geometries(geom, b, h, w, dtype):
+    cin, cout, k, s, d, g = geom
+    kt = torch.from_numpy(rand((cout, cin // g, k, k), 6)).to(DEV)
+    if dtype == "bf16":
+        kt = kt.to(torch.bfloat16)
+    k64 = kt.double().cpu().numpy()
+    for transposed in (False, True):
+        x = rand((b, cout, h // s, w // s) if transposed else (b, cin, h, w), 7)
+        at = tuple(v - 1 - (v > 2) for v in x.shape)   # in the last channels, off the corner
+        apply64 = lambda kk, v: (conv.conv_circular_adjoint(kk, v, (h, w), s, d, g) if transposed else   # noqa: E731
+                                 conv.conv_circular(kk, v, s, d, g))
+        x[at] = 0.0
+        ref = apply64(k64, x.astype(np.float64))
+        one = np.zeros_like(x, dtype=np.float64)
+        one[at] = 1.0
+        hit = apply64(np.abs(k64), one) > 0
+        x[at] = np.inf
+        got = orth.orth_conv_apply(kt, geom, torch.from_numpy(x).to(DEV), transposed=transposed).cpu().numpy()
+        assert not np.isfinite(got[hit]).any() and hit.any()
+        if not hit.all():
+            assert checks.relative_difference(got[~hit][None].astype(np.float64), ref[~hit][None]) <= REL

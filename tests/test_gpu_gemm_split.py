@@ -8,7 +8,7 @@ import numpy as np
 import pytest
 import torch
 
-from oracle import bjorck, bjorck_grad, checks, expo, spectral
+from oracle import aoc, aoc_grad, bjorck, bjorck_grad, checks, expo, spectral
 from paper_2601_13776_amd import orth
 
 pytestmark = pytest.mark.gpu
@@ -155,6 +155,48 @@ def test_nonfinite_products(c, og):
         assert np.isfinite(got[rows]).all()
         scale = np.abs(ref64[rows]).max()
         assert checks.relative_difference(got[rows] / scale, ref64[rows] / scale) <= TOL
+
+
+# compositions and their VJP with enough 128-tiles for every compute unit:
+# k-major products with ragged M and N (388) and ones that are no multiple of
+# four (387), row-major ones with a remainder of K (194, 193), fp32 and
+# bfloat16 operands, whole and per 128-block; a layer of non-finite values
+# (on fp32 products) leaves the others alone
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c", [388, 387])
+def test_big_tile_compositions(c, dtype):
+    n, geom, tol = 16, (c, c, 3, 1, 1, 1), TOL if dtype == "f32" else 4e-3   # one bfloat16 rounding
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dev = lambda a: torch.from_numpy(a).to(DEV).to(dt).contiguous()   # noqa: E731
+    rko = [_rand(60 + i, 1, c, c) for i in range(n)]
+    proj = [(_rand(80 + i, 1, 4, c, c // 2) / np.sqrt(c)).astype(np.float32) for i in range(n)]
+    dk = [_rand(100 + i, c, c, 3, 3) for i in range(n)]
+    bad = 5
+    rko[bad][0, 7, 3] = np.inf
+    dk[bad][9, 4, 1, 1] = np.nan
+    layers = [dict(geom=geom, rko=dev(r), proj=dev(p), kernel=torch.empty(c, c, 3, 3, dtype=dt, device=DEV),
+                   grad_kernel=dev(g), grad_rko=torch.empty(1, c, c, dtype=dt, device=DEV),
+                   grad_proj=torch.empty(1, 4, c, c // 2, dtype=dt, device=DEV))
+              for r, p, g in zip(rko, proj, dk)]
+    orth.orth_build_conv_kernels_batched(layers)
+    orth.orth_build_conv_kernels_vjp_batched(layers)
+    f64 = lambda t: t.double().cpu().numpy()   # noqa: E731
+    for i in (0, n - 1):
+        L = layers[i]
+        r64, p64, g64 = f64(L["rko"]), f64(L["proj"]), f64(L["grad_kernel"])
+        got = f64(L["kernel"])
+        ref = aoc.aoc_kernel(r64, p64, *geom)
+        pairs = [(got[:, :, a, b], ref[:, :, a, b]) for a in range(3) for b in range(3)]
+        dr, dp = aoc_grad.aoc_kernel_vjp(r64, p64, *geom, g64)
+        pairs += [(f64(L["grad_rko"])[0], dr[0])]
+        pairs += [(f64(L["grad_proj"])[0, t], dp[0, t]) for t in range(4)]
+        for a, b in pairs:
+            assert checks.tile_relative_differences(a, b, 128).max() <= tol
+    for i, L in enumerate(layers):
+        fin = [bool(torch.isfinite(L[k]).all()) for k in ("kernel", "grad_rko", "grad_proj")]
+        assert fin == [i != bad] * 3, (i, fin)
+    rows = torch.isfinite(layers[bad]["kernel"].float()).flatten(1).all(1)
+    assert rows.sum() == c - 1 and not rows[7]
 
 
 # gradients of any power-of-two scale give the same result times that scale,
