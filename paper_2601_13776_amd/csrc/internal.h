@@ -125,8 +125,13 @@ __device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint3
 
 // Whether split products cannot stand for a result of theirs: it is not
 // finite (an infinity splits into inf - inf, a value past bfloat16's largest
-// into an infinity).
-__device__ __forceinline__ bool split_failed(float v) { return !isfinite(v); }
+// into an infinity), or it is so small (but not zero) that low pieces of its
+// operands may have fallen off the end of bfloat16's range.
+__device__ __forceinline__ bool split_failed(float v) {
+  constexpr uint32_t lo = 0x0d800000u, hi = 0x7f800000u;   // 2^-100, infinity
+  const uint32_t u = __float_as_uint(v) & 0x7fffffffu;
+  return u != 0 && u - lo >= hi - lo;
+}
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
 

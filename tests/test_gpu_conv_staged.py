@@ -112,3 +112,18 @@ def test_nonfinite_geometries(geom, b, h, w, dtype):
         assert not np.isfinite(got[hit]).any() and hit.any()
         if not hit.all():
             assert checks.relative_difference(got[~hit][None].astype(np.float64), ref[~hit][None]) <= REL
+
+
+# inputs near the low end of fp32 keep its accuracy (their low pieces would
+# not; the tiles are computed with fp32 products)
+@pytest.mark.parametrize("transposed", [False, True])
+@pytest.mark.parametrize("exp", [-104, -120])
+def test_small_inputs(exp, transposed):
+    geom = (16, 24, 3, 2, 1, 1)
+    kern = rand((24, 16, 3, 3), 8)
+    x = rand((2, 24, 6, 6) if transposed else (2, 16, 12, 12), 9) * np.float32(2.0 ** exp)
+    got = orth.orth_conv_apply(torch.from_numpy(kern).to(DEV), geom, torch.from_numpy(x).to(DEV),
+                               transposed=transposed).cpu().numpy().astype(np.float64)
+    k64, x64 = kern.astype(np.float64), x.astype(np.float64)
+    ref = conv.conv_circular_adjoint(k64, x64, (12, 12), 2) if transposed else conv.conv_circular(k64, x64, 2)
+    assert checks.relative_difference(got * 2.0 ** -exp, ref * 2.0 ** -exp) <= 1e-6   # (fp32 sums of 144 terms)

@@ -199,6 +199,14 @@ def test_big_tile_compositions(c, dtype):
     assert rows.sum() == c - 1 and not rows[7]
 
 
+# values near the low end of fp32 keep its accuracy without pre-scaling: E is
+# the identity to fp32, so a step multiplies them by 3/2
+def test_small_values():
+    m = _rand(16, 192, 130) * np.float32(2.0 ** -120)
+    got = _run([m], 3, prescale="none")[0]
+    assert checks.relative_difference(got * 2.0 ** 120, m.astype(np.float64) * (2.0 ** 120 * 3.375)) <= 1e-6
+
+
 # gradients of any power-of-two scale give the same result times that scale,
 # bit for bit (the products scale them themselves)
 @pytest.mark.parametrize("exp", [-90, -23, 17, 60])
