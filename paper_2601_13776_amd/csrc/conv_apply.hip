@@ -298,6 +298,60 @@ typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x4_a2 __attribute__((ext_vector_type(4), aligned(2)));
 typedef uint32_t u32x2_a2 __attribute__((ext_vector_type(2), aligned(2)));
 
+// A wave's 32 x 32 block with fp32 MFMA: this lane's channel `row` of the
+// group (as MFMA row) and output pixel (as column), by the formula.  16
+// channels of one tap at a time straight from memory (the lower lanes hold
+// the first eight, the upper ones the others; all taps of 16 channels before
+// the next 16, so that the kernel's lines are read whole); loads past an end
+// re-read the last value and count as zero (byte offsets fit 32 bits, see
+// stage_geom).  Done early where every value is NaN already.
+template <bool TR>
+__device__ __forceinline__ f32x16 conv_block_f32(const ApplyGeom& G, const void* kern, const float* x, int grp,
+                                                 int row, bool pix_ok, int b, int p, int q) {
+  constexpr int CN = 8;   // (a lane half's channels)
+  f32x16 acc = {};
+  const int kk2 = G.k * G.k, nch = TR ? G.og : G.c, chh = CN * ((threadIdx.x >> 5) & 1);
+  const uint32_t cplane = TR ? G.Ho * G.Wo : G.H * G.W, kch = TR ? G.c * kk2 : kk2;   // between channels
+  const uint32_t rc = row < G.rows ? row : G.rows - 1;
+  const uint32_t k0 = TR ? (grp * G.og * G.c + rc) * kk2 : (grp * G.og + rc) * G.red;
+  const uint32_t x0 = (b * (TR ? G.cout : G.cin) + grp * nch) * cplane;
+  const bool row_ok = row < G.rows, narrow = G.kdtype == ORTH_BF16;
+#pragma unroll 1
+  for (int ch0 = 0; ch0 < nch; ch0 += 2 * CN) {
+    const int ch = ch0 + chh;
+#pragma unroll 1
+    for (int tap = 0; tap < kk2; ++tap) {
+      const int a = tap / G.k, e = tap - a * G.k;
+      int r = pmod(TR ? p + G.pl - G.d * a : G.s * p + G.d * a - G.pl, G.H);
+      int c = pmod(TR ? q + G.pl - G.d * e : G.s * q + G.d * e - G.pl, G.W);
+      const bool hit = pix_ok && (!TR || (r % G.s == 0 && c % G.s == 0));
+      if (!__any(hit)) continue;
+      if (TR) {
+        r /= G.s;
+        c /= G.s;
+      }
+      const uint32_t xt = x0 + r * (TR ? G.Wo : G.W) + c, kt = k0 + tap;
+      uint32_t av[CN], bv[CN];
+#pragma unroll
+      for (int i = 0; i < CN; ++i) {
+        const uint32_t cc = ch + i < nch ? ch + i : nch - 1;
+        const uint32_t ko = kt + cc * kch, xo = (xt + cc * cplane) * 4;
+        const char* kp = static_cast<const char*>(kern);
+        av[i] = narrow ? (uint32_t)gld_u16(kp + ko * 2u, 0) << 16 : gld_u32(kp + ko * 4u, 0);
+        bv[i] = gld_u32(reinterpret_cast<const char*>(x) + xo, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < CN; ++i) {
+        const bool in = ch + i < nch;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(in && row_ok ? __uint_as_float(av[i]) : 0.f,
+                                                   in && hit ? __uint_as_float(bv[i]) : 0.f, acc, 0, 0, 0);
+      }
+    }
+    if (__all(all_nan(acc) || !pix_ok)) break;
+  }
+  return acc;
+}
+
 template <bool TR, int KS, int PH, bool KBF16, int PU>
 __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, StageGeom T,
                                                                    const void* __restrict__ kern,
@@ -555,111 +609,13 @@ __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, 
     }
   }
 
-  // the grid position of this lane's pixel in block i (PH == 4: in every block)
-  auto pixel = [&](int i) { return p0 + wn * (BN / 2) + (PH == 4 ? 0 : i * 32) + (lane & 31); };
-  uint32_t redo = 0;   // this wave's blocks that fp32 MFMA has to compute
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    bool bad = false;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      acc[0][i][r] += acc[1][i][r];
-      bad |= split_failed(acc[0][i][r]);
-    }
-    redo |= __any(bad && pixel(i) < T.pix) ? 1u << i : 0u;
-  }
-  uint32_t* const votes = reinterpret_cast<uint32_t*>(smem4);
-  __syncthreads();   // the last chunk is read
-  if (lane == 0) votes[wave] = redo;
-  __syncthreads();
-  const int redo_tile = __builtin_amdgcn_readfirstlane(votes[0] | votes[1] | votes[2] | votes[3]);
-  if (__builtin_expect(redo_tile != 0, 0)) {
-    // The tile on fp32 MFMA from fp32 values in the same places: groups of 8
-    // channels per (entry, row) (a bfloat16 kernel stays as it is) and per
-    // position; a wave's halves hold the even and the odd four channels of a
-    // group.  The blocks that asked for it take the result.
-    float* const Af = reinterpret_cast<float*>(As);
-    float* const Xf = reinterpret_cast<float*>(Xs);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) acc[1][i] = f32x16{};
-    // (its own offsets: with those of the pass above the compiler keeps whole
-    // addresses for both, 100 registers more at k = 1)
-#pragma unroll
-    for (int i = 0; i < PU; ++i) asm volatile("" : "+v"(xoff[i]));
-    load(0);
-    for (int ch0 = 0; ch0 < T.nch; ch0 += CB) {
-      __syncthreads();
-#pragma unroll
-      for (int g = 0; g < G8; ++g)
-#pragma unroll
-        for (int t = 0; t < KK; ++t) {
-          const int dst = entry(t, g) * 64 + krow;
-          const int left = T.nch - (ch0 + 8 * g + 2 * kc2);   // channels past the end are zero
-          if constexpr (KBF16) {
-            uint32_t a = (ra[g][0][t / 2] >> (t & 1 ? 16 : 0)) & 0xffffu;
-            uint32_t b = (ra[g][1][t / 2] >> (t & 1 ? 16 : 0)) & 0xffffu;
-            reinterpret_cast<uint32_t*>(As)[dst * 4 + kc2] = (left > 0 ? a : 0u) | (left > 1 ? b << 16 : 0u);
-          } else {
-            Af[dst * 8 + 2 * kc2] = left > 0 ? __uint_as_float(ra[g][0][t]) : 0.f;
-            Af[dst * 8 + 2 * kc2 + 1] = left > 1 ? __uint_as_float(ra[g][1][t]) : 0.f;
-          }
-        }
-#pragma unroll
-      for (int i = 0; i < PU; ++i) {
-        const int pos = tid + i * 256;
-        if (pos < T.npos) {
-#pragma unroll
-          for (int g = 0; g < G8; ++g)
-#pragma unroll
-            for (int c = 0; c < 8; ++c)
-              Xf[(g * T.npos + pos) * 8 + c] = ch0 + 8 * g + c < T.nch ? rx[i][g][c] : 0.f;
-        }
-      }
-      __syncthreads();
-      load(ch0 + CB < T.nch ? ch0 + CB : ch0);
-#pragma unroll
-      for (int g = 0; g < G8; ++g)
-#pragma unroll
-        for (int t = 0; t < KK; ++t) {
-          const int at = entry(t, g) * 64 + arow, a = t / KS, e = t % KS;
-          const int off = g * T.npos + (KS == 1 ? 0 : (T.rows_sep ? a : T.rt[a] - T.rmin) * T.WX + (T.ct[e] - T.cmin));
-          float fa[4];
-          if constexpr (KBF16) {
-            const uint2 w = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint32_t*>(As) + at * 4 + 2 * half);
-            fa[0] = __uint_as_float(w.x << 16);
-            fa[1] = __uint_as_float(w.x & 0xffff0000u);
-            fa[2] = __uint_as_float(w.y << 16);
-            fa[3] = __uint_as_float(w.y & 0xffff0000u);
-          } else {
-            const float4 w = *reinterpret_cast<const float4*>(Af + at * 8 + 4 * half);
-            fa[0] = w.x; fa[1] = w.y; fa[2] = w.z; fa[3] = w.w;
-          }
-#pragma unroll
-          for (int i = 0; i < (PH == 4 ? 1 : NB); ++i) {
-            const float4 w = *reinterpret_cast<const float4*>(Xf + (poff[i] + off) * 8 + 4 * half);
-            const float fb[4] = {w.x, w.y, w.z, w.w};
-            f32x16& sum = acc[1][PH == 4 ? phase_of(entry(t, g) >> 1) : i];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[c], fb[c], sum, 0, 0, 0);
-          }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-      if (redo >> i & 1) acc[0][i] = acc[1][i];
-  }
-
-  // columns are pixels: consecutive lanes store consecutive pixels
-  const int oh = TR ? G.H : G.Ho, ow = TR ? G.W : G.Wo;
-  const int ych = TR ? G.cin : G.cout, chb = grp * (TR ? G.c : G.og);
-  const int64_t plane = (int64_t)oh * ow;
-#pragma unroll
-  for (int i = 0; i < NB; ++i) {
-    const int64_t pn = pixel(i);
-    if (pn >= T.pix) continue;
+  // this lane's output of block i: sample and position; false past the end
+  auto output = [&](int i, int& b, int& u, int& v) -> bool {
+    const int64_t pn = p0 + wn * (BN / 2) + (PH == 4 ? 0 : i * 32) + (lane & 31);
     const int64_t orow = pn / T.Wg;
-    const int b = (int)(orow / T.Hg);
-    int u = (int)(orow - (int64_t)b * T.Hg), v = (int)(pn - orow * T.Wg);
+    b = (int)(orow / T.Hg);
+    u = (int)(orow - (int64_t)b * T.Hg);
+    v = (int)(pn - orow * T.Wg);
     if (PH == 4) {   // block i holds the taps of row parity i / 2, column parity i % 2
       u = 2 * u + ((i >> 1) ^ T.par);
       v = 2 * v + ((i & 1) ^ T.par);
@@ -667,6 +623,34 @@ __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, 
       u = T.os * u + pfh;
       v = T.os * v + pfw;
     }
+    return pn < T.pix;
+  };
+  uint32_t failed = 0;   // this wave's blocks that the split cannot give
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    acc[0][i] += acc[1][i];
+    failed |= __any(split_failed(acc[0][i])) ? 1u << i : 0u;
+  }
+  if (__builtin_expect(failed != 0, 0)) {
+#pragma unroll 1
+    for (int n = 0; n < NB; ++n) {
+      if (!(failed >> n & 1)) continue;
+      int b, u, v;
+      const bool ok = output(n, b, u, v);
+      const f32x16 t = conv_block_f32<TR>(G, kern, x, grp, row0 + wm * 32 + (lane & 31), ok, ok ? b : 0, u, v);
+#pragma unroll
+      for (int i = 0; i < NB; ++i)
+        if (i == n) acc[0][i] = t;
+    }
+  }
+  // columns are pixels: consecutive lanes store consecutive pixels
+  const int oh = TR ? G.H : G.Ho, ow = TR ? G.W : G.Wo;
+  const int ych = TR ? G.cin : G.cout, chb = grp * (TR ? G.c : G.og);
+  const int64_t plane = (int64_t)oh * ow;
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    int b, u, v;
+    if (!output(i, b, u, v)) continue;
     float* yp = y + ((int64_t)b * ych + chb) * plane + (int64_t)u * ow + v;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {

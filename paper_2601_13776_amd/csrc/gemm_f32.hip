@@ -19,11 +19,13 @@
 // 1.3e-7 / 4.0e-7 (one accumulator for all: 1.1e-7 / 3.4e-7 / 1.0e-6).  Two
 // half pieces take half the products, but 22 bits and half's range: light
 // rows and columns beside heavy ones lost theirs.
-// A tile with a result that the split cannot give (split_failed: infinities,
+// A wave's block with a result that the split cannot give (split_failed: infinities,
 // NaN, overflow, values near the low end of fp32) is computed again with fp32
-// MFMA, its operands staged through LDS like the pieces are.  Conv
-// exponentials of 256 channels, one NaN in the kernel: 1.80 ms (0.91 without;
-// 1.23 when every tile ran on fp32 MFMA).
+// MFMA by the wave that meets it, straight from memory (through LDS, by vote
+// of the workgroup, took 1.80 ms where this takes 1.36, and 0.2 us more of
+// every launch): conv exponentials of 256 channels, 0.89 ms, with one NaN in
+// the kernel 1.36, scaled until they overflow 0.85 (1.23 to 1.34 when every
+// tile ran on fp32 MFMA).
 //
 // Lists with a 128-tile for every compute unit use those (half the splitting
 // and LDS writes per product), others 64.
@@ -93,6 +95,71 @@ __device__ __forceinline__ PairView pair_view(const GemmItem& g, const GemmPair*
     v.btr = x->b_trans;
   }
   return v;
+}
+
+// The wave's 32 x 32 block at (i0, j0) with fp32 MFMA: the blocks whose split
+// result fails.  16 k at a time straight from memory (the lower lanes hold
+// the first eight, the upper ones the others), the next 16 on their way;
+// done early where every value is NaN already.
+__device__ __forceinline__ f32x16 block_f32(const GemmItem& g, const GemmPair* extra, int64_t st, int i0,
+                                            int j0) {
+  const int lane = threadIdx.x & 63, kh = 8 * (lane >> 5);
+  f32x16 acc = {};
+  const int npairs = 2 + g.pair_count;
+#pragma unroll 1
+  for (int pair = 0; pair < npairs; ++pair) {
+    const PairView v = pair_view(g, extra, pair, st);
+    const char* at[2];       // the next of this lane's values
+    int64_t ks[2];           // bytes between them
+    bool in[2], narrow[2];
+#pragma unroll
+    for (int o = 0; o < 2; ++o) {
+      const int row = (o ? j0 : i0) + (lane & 31);
+      const int64_t ld = o ? v.ldb : v.lda;
+      const bool tr = (o ? v.btr : v.atr) != 0;
+      narrow[o] = (o ? g.b_dtype : g.a_dtype) == ORTH_BF16;
+      in[o] = row < (o ? g.N : g.M);
+      const int64_t vb = narrow[o] ? 2 : 4;
+      ks[o] = (tr ? ld : 1) * vb;
+      at[o] = (o ? v.B : v.A) + (in[o] ? tr ? row * vb : row * ld * vb : 0) + kh * ks[o];
+    }
+    uint32_t w[2][8];
+    // the values of the step at k, as they are stored; zeros past the end
+    // (rows past it re-read the first one: their results are not stored)
+    auto load = [&](int k) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        if (k + 16 <= v.K && ks[o] == 4) {
+          const uint4 a = gld_u32x4_a4(reinterpret_cast<const float*>(at[o]));
+          const uint4 b = gld_u32x4_a4(reinterpret_cast<const float*>(at[o]) + 4);
+          w[o][0] = a.x; w[o][1] = a.y; w[o][2] = a.z; w[o][3] = a.w;
+          w[o][4] = b.x; w[o][5] = b.y; w[o][6] = b.z; w[o][7] = b.w;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) {
+            w[o][q] = 0;
+            if (in[o] && k + kh + q < v.K)
+              w[o][q] = narrow[o] ? (uint32_t)gld_u16(at[o] + q * ks[o], 0) : gld_u32(at[o] + q * ks[o], 0);
+          }
+        }
+        at[o] += 16 * ks[o];
+      }
+    };
+    load(0);
+#pragma unroll 1
+    for (int k0 = 0; k0 < v.K; k0 += 16) {
+      float x[2][8];
+#pragma unroll
+      for (int o = 0; o < 2; ++o)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[o][q] = __uint_as_float(w[o][q] << (narrow[o] ? 16 : 0));
+      load(k0 + 16);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][q], x[1][q], acc, 0, 0, 0);
+      if (k0 % 128 == 0 && __all(all_nan(acc))) return acc;
+    }
+  }
+  return acc;
 }
 
 // MODE: the operands of every tile of the launch are GEMM_ROWS all fp32 and
@@ -360,80 +427,18 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NI; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const float v = acc[0][i][j][r] + acc[1][i][j][r];
-        acc[0][i][j][r] = v;
-        bad |= split_failed(v);
-      }
-  bool redo = __any(bad);
-  if (__builtin_expect(redo, 0)) {
-    // every row of the wave's part of A starts with a NaN: so does the
-    // fp32 result (a matrix that is NaN throughout)
-    bool all_nan = true;
-    for (int i = 0; i < MI; ++i) {
-      const int r = row0 + wm * (BM / WM) + i * 32 + (lane & 31);
-      if (r < M && item.K > 0) {
-        const PairView v = pair_view(item, extra, 0, st);
-        const float a = load_as_f32(v.A, v.atr ? r : r * v.lda, item.a_dtype);
-        all_nan &= isnan(a);
-      } else if (r < M) {
-        all_nan = false;
-      }
+    for (int j = 0; j < NI; ++j) {
+      acc[0][i][j] += acc[1][i][j];
+      bad |= split_failed(acc[0][i][j]);
     }
-    redo = !__all(all_nan);
-  }
-  // (the votes lie past what the epilogues use)
-  int* const votes = reinterpret_cast<int*>(smem) + 2 * 2 * P * BM * CH * 4 - WM * WN;
-  if (lane == 0) votes[wave] = redo;
-  __syncthreads();
-  int redo_tile = 0;
+  if (__builtin_expect(__any(bad), 0)) {
+#pragma unroll 1
+    for (int n = 0; n < MI * NI; ++n) {
+      const f32x16 t = block_f32(item, extra, st, row0 + wm * (BM / WM) + n / NI * 32,
+                                 col0 + wn * (BM / WN) + n % NI * 32);
 #pragma unroll
-  for (int w = 0; w < WM * WN; ++w) redo_tile |= votes[w];
-  if (__builtin_expect(__builtin_amdgcn_readfirstlane(redo_tile) != 0, 0)) {
-    // The tile on fp32 MFMA, its operands' fp32 values through LDS, a step
-    // at a time; the waves that asked for it take the result.
-    constexpr int LD = BK + 1;
-    float* const F = reinterpret_cast<float*>(smem);   // [operand][BM rows][LD]
-#pragma unroll
-    for (int i = 0; i < MI; ++i)
-#pragma unroll
-      for (int j = 0; j < NI; ++j) acc[1][i][j] = f32x16{};
-    for (int p = 0; p < npairs; ++p) {
-      const PairView v = pair_view(item, extra, p, st);
-      for (int k0 = 0; k0 < v.K; k0 += BK) {
-        float x[2][8];
-        bool tro[2];
-#pragma unroll
-        for (int o = 0; o < 2; ++o) tro[o] = load_guarded(v, k0, o, x[o]);
-        __syncthreads();   // the votes, or the step before, are read
-#pragma unroll
-        for (int o = 0; o < 2; ++o)
-#pragma unroll
-          for (int q = 0; q < 8; ++q)
-            F[(o * BM + (tro[o] ? tr + (q & 3) : rr)) * LD + (tro[o] ? tk + (q >> 2) : rc * 8 + q)] = x[o][q];
-        __syncthreads();
-        for (int kk = 0; kk < BK; kk += 2) {
-          float fa[MI], fb[NI];
-#pragma unroll
-          for (int i = 0; i < MI; ++i) fa[i] = F[(wm * (BM / WM) + i * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
-#pragma unroll
-          for (int j = 0; j < NI; ++j) fb[j] = F[(BM + wn * (BM / WN) + j * 32 + (lane & 31)) * LD + kk + (lane >> 5)];
-#pragma unroll
-          for (int i = 0; i < MI; ++i)
-#pragma unroll
-            for (int j = 0; j < NI; ++j)
-              acc[1][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[1][i][j], 0, 0, 0);
-        }
-      }
-    }
-    __syncthreads();   // the epilogue reuses LDS
-    if (redo) {
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NI; ++j) acc[0][i][j] = acc[1][i][j];
+      for (int i = 0; i < MI * NI; ++i)
+        if (i == n) acc[0][i / NI][i % NI] = t;
     }
   }
 

@@ -123,14 +123,29 @@ __device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint3
   l = cvt2_bf16(ra - __uint_as_float(m << 16), rb - __uint_as_float(m & 0xffff0000u));
 }
 
-// Whether split products cannot stand for a result of theirs: it is not
+// Whether split products cannot stand for a lane's 16 results: one is not
 // finite (an infinity splits into inf - inf, a value past bfloat16's largest
-// into an infinity), or it is so small (but not zero) that low pieces of its
-// operands may have fallen off the end of bfloat16's range.
-__device__ __forceinline__ bool split_failed(float v) {
-  constexpr uint32_t lo = 0x0d800000u, hi = 0x7f800000u;   // 2^-100, infinity
-  const uint32_t u = __float_as_uint(v) & 0x7fffffffu;
-  return u != 0 && u - lo >= hi - lo;
+// into an infinity), or the largest is so small (but not zero) that low
+// pieces of its operands may have fallen off the end of bfloat16's range.
+// (Value by value the second test took 0.2 us more of every launch.)
+template <typename V16>
+__device__ __forceinline__ bool split_failed(const V16& v) {
+  float top = 0.f, nan0 = 0.f, nan1 = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    top = fmaxf(fmaxf(top, fabsf(v[r])), fabsf(v[r + 1]));
+    nan0 = fmaf(v[r], 0.f, nan0);
+    nan1 = fmaf(v[r + 1], 0.f, nan1);
+  }
+  return !(nan0 + nan1 == 0.f) || (top > 0.f && top < 0x1p-100f);
+}
+
+template <typename V16>
+__device__ __forceinline__ bool all_nan(const V16& v) {
+  bool any = false;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) any |= v[r] == v[r];
+  return !any;
 }
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(127 + e) << 23); }
