@@ -45,6 +45,7 @@ __device__ inline int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane
 // 16 bytes from any 4-byte aligned global address (gfx950 needs no more for
 // multi-dword accesses)
 typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(2)));   // (or 2-byte aligned)
 __device__ __forceinline__ uint4 gld_u32x4_a4(const float* p) {
   const u32x4u v = *(const ORTH_GLOBAL u32x4u*)p;
   return make_uint4(v.x, v.y, v.z, v.w);
@@ -274,52 +275,70 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
                         __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
     split_store(x, MODE == GEMM_KMAJOR, s, o);
   };
-  // this thread's values of operand o at k0 of pair v, a whole step or not
-  // (zeros past the end); returns whether they lie k-major
-  auto load_guarded = [&](const PairView& v, int k0, int o, float (&x)[8]) -> bool {
+  // What the pipeline leaves: this thread's values of operand o at k0 of pair
+  // v, a whole step or not (zeros past the end), as they are stored: words of
+  // fp32, of one bfloat16 each, or (four words) of two.
+  enum { WORDS_F32, WORDS_BF16, WORDS_2BF16 };
+  auto k_major = [&](const PairView& v, int o) {
+    return MODE == GEMM_KMAJOR || (MODE == GEMM_ANY && (o ? v.btr : v.atr) != 0);
+  };
+  auto load_guarded = [&](const PairView& v, int k0, int o, uint32_t (&w)[8]) -> int {
     const char* ptr = o ? v.B : v.A;
     const int64_t ld = o ? v.ldb : v.lda;
-    const bool tro = MODE == GEMM_KMAJOR || (MODE == GEMM_ANY && (o ? v.btr : v.atr) != 0);
+    const bool tro = k_major(v, o);
     const int dt = o ? bdt : adt, base = o ? col0 : row0, lim = o ? N : M;
-    if (k0 + BK <= v.K && dt == ORTH_F32 && (!tro || base + BM <= lim || lim % 4 == 0)) {
+    if (MODE == GEMM_ANY && k0 + BK <= v.K && (!tro || base + BM <= lim || lim % 4 == 0)) {
       const int r = tro ? (base + tr + 4 <= lim ? base + tr : lim - 4) : (base + rr < lim ? base + rr : lim - 1);
-      const float* p = reinterpret_cast<const float*>(ptr) +
-                       (tro ? (int64_t)(k0 + tk) * ld + r : (int64_t)r * ld + k0 + rc * 8);
-      const uint4 a = gld_u32x4_a4(p), b = gld_u32x4_a4(tro ? p + ld : p + 4);
-      x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y); x[2] = __uint_as_float(a.z);
-      x[3] = __uint_as_float(a.w); x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
-      x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
-    } else if (MODE == GEMM_ANY && k0 + BK <= v.K && dt == ORTH_BF16 && !tro && vec8_ok(ptr, ld, ORTH_BF16)) {
-      load8_f32(ptr, (int64_t)(base + rr < lim ? base + rr : lim - 1) * ld + k0 + rc * 8, ORTH_BF16, x);
-    } else {
-      // (raw bits first: a conversion inside the guarded load would make
-      // every load wait for its data)
-      uint32_t w[8];
+      const int64_t e = tro ? (int64_t)(k0 + tk) * ld + r : (int64_t)r * ld + k0 + rc * 8;
+      if (dt == ORTH_F32) {
+        const float* p = reinterpret_cast<const float*>(ptr) + e;
+        const uint4 a = gld_u32x4_a4(p), b = gld_u32x4_a4(tro ? p + ld : p + 4);
+        w[0] = a.x; w[1] = a.y; w[2] = a.z; w[3] = a.w;
+        w[4] = b.x; w[5] = b.y; w[6] = b.z; w[7] = b.w;
+        return WORDS_F32;
+      }
+      const uint16_t* p = reinterpret_cast<const uint16_t*>(ptr) + e;
+      const u32x2u a = *(const ORTH_GLOBAL u32x2u*)p, b = *(const ORTH_GLOBAL u32x2u*)(tro ? p + ld : p + 4);
+      w[0] = a.x; w[1] = a.y; w[2] = b.x; w[3] = b.y;
+      return WORDS_2BF16;
+    }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int r = base + (tro ? tr + (q & 3) : rr), k = k0 + (tro ? tk + (q >> 2) : rc * 8 + q);
-        w[q] = 0;
-        if (r < lim && k < v.K) {
-          const int64_t e = tro ? (int64_t)k * ld + r : (int64_t)r * ld + k;
-          w[q] = dt == ORTH_BF16 ? (uint32_t)gld_u16(ptr, e) : gld_u32(ptr, e);
+    for (int q = 0; q < 8; ++q) {
+      const int r = base + (tro ? tr + (q & 3) : rr), k = k0 + (tro ? tk + (q >> 2) : rc * 8 + q);
+      w[q] = 0;
+      if (r < lim && k < v.K) {
+        const int64_t e = tro ? (int64_t)k * ld + r : (int64_t)r * ld + k;
+        w[q] = dt == ORTH_BF16 ? (uint32_t)gld_u16(ptr, e) : gld_u32(ptr, e);
+      }
+    }
+    return dt == ORTH_BF16 ? WORDS_BF16 : WORDS_F32;
+  };
+  // those words -> LDS stage s (of two bfloat16 the leading piece alone: the
+  // products of the others are left out)
+  auto store_guarded = [&](const uint32_t (&w)[8], int form, bool tro, int s, int o) {
+    if (MODE == GEMM_ANY && form == WORDS_2BF16) {
+      if (!tro) {
+        plane(s, o, 0)[rr * CH + (rc ^ swz(rr))] = make_uint4(w[0], w[1], w[2], w[3]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = tr + j, dst = (r * CH + ((tk >> 3) ^ swz(r))) * 4 + ((tk & 7) >> 1);
+          const uint32_t a = w[j >> 1], b = w[2 + (j >> 1)];
+          reinterpret_cast<uint32_t*>(plane(s, o, 0))[dst] =
+              j & 1 ? (a >> 16) | (b & 0xffff0000u) : (a & 0xffffu) | (b << 16);
         }
       }
-      const int sh = dt == ORTH_BF16 ? 16 : 0;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        asm volatile("" : "+v"(w[q]));
-        x[q] = __uint_as_float(w[q] << sh);
-      }
+      return;
     }
-    return tro;
-  };
-  auto stage_guarded = [&](const PairView& v, int k0, int s) {
+    const int sh = form == WORDS_BF16 ? 16 : 0;
+    float x[8];
 #pragma unroll
-    for (int o = 0; o < 2; ++o) {
-      float x[8];
-      const bool tro = load_guarded(v, k0, o, x);
-      split_store(x, tro, s, o);
+    for (int q = 0; q < 8; ++q) {
+      uint32_t u = w[q];
+      asm volatile("" : "+v"(u));   // (no conversion inside the guarded load: it would wait for each)
+      x[q] = __uint_as_float(u << sh);
     }
+    split_store(x, tro, s, o);
   };
 
   f32x16 acc[2][MI][NI];   // the leading products, the corrections
@@ -348,9 +367,12 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
       }
     }
   };
+  // (bfloat16 operands are their own leading piece)
+  const bool a_one = MODE == GEMM_ANY && adt == ORTH_BF16, b_one = MODE == GEMM_ANY && bdt == ORTH_BF16;
   auto mfmas = [&](const Frags& f) {
 #pragma unroll
-    for (int q = 0; q < NP; ++q)
+    for (int q = 0; q < NP; ++q) {
+      if ((a_one && prod_a(q) > 0) || (b_one && prod_b(q) > 0)) continue;
 #pragma unroll
       for (int i = 0; i < MI; ++i)
 #pragma unroll
@@ -358,6 +380,7 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
           f32x16& t = acc[q < NP - 1][i][j];
           t = mma(f.a[i][prod_a(q)], f.b[j][prod_b(q)], t);
         }
+    }
   };
   // The pipeline.  Step t's halves lie in LDS stage t & 1.  First half: the
   // second half's fragments are read, operand B of step t + 1 is split into
@@ -411,7 +434,12 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
     for (int p = 0; p < npairs; ++p) {
       const PairView v = pair_view(item, extra, p, st);
       for (int k0 = MODE == GEMM_ANY ? 0 : v.K / BK * BK; k0 < v.K; k0 += BK, s ^= 1) {
-        stage_guarded(v, k0, s);
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+          uint32_t w[8];
+          const int form = load_guarded(v, k0, o, w);
+          store_guarded(w, form, k_major(v, o), s, o);
+        }
         __syncthreads();
         for (int kk = 0; kk < BK / 16; ++kk) {
           read_frags(s, kk, f0);

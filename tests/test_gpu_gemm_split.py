@@ -62,6 +62,19 @@ def test_gram_of_long_strides(rows, cols, ld):
     assert abs(got - ref) <= TOL * max(1.0, ref)
 
 
+# bfloat16 operands (their own leading piece): rows and k-major, whole steps
+# and remainders, tiles that end on a multiple of four rows and that do not,
+# views that are only 2-byte aligned
+@pytest.mark.parametrize("shape", [(96, 64), (64, 96), (100, 68), (72, 300), (257, 33), (130, 131), (320, 130)])
+@pytest.mark.parametrize("offset", [0, 1])
+def test_gram_of_bf16(shape, offset):
+    buf = torch.from_numpy(_rand(17, shape[0], shape[1] + 3)).to(DEV).to(torch.bfloat16)
+    view = buf[:, offset:offset + shape[1]]
+    got = float(orth.orth_check_norm_gram([view])[0])
+    ref = checks.gram_deviation(view.double().cpu().numpy())
+    assert abs(got - ref) <= TOL * max(1.0, ref)
+
+
 # light rows keep their own relative accuracy beside rows 2^10 times larger
 def test_row_scales():
     m = _rand(3, 192, 128)
