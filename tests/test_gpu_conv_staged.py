@@ -24,6 +24,8 @@ CASES = [  # (cin, cout, k, s, d, g), batch, H, W
     ((12, 20, 3, 2, 3, 2), 3, 14, 10), ((66, 9, 3, 2, 1, 1), 1, 2, 2),
     # k = s = 3: one tap per output phase
     ((10, 35, 3, 3, 1, 1), 2, 12, 9), ((6, 8, 3, 3, 2, 2), 2, 9, 15),
+    # stride 3 forward: most staged positions per thread
+    ((9, 20, 3, 3, 1, 1), 3, 27, 27),
     # large dilations: staged rows per grid row; more than two positions per thread
     ((8, 16, 3, 1, 6, 1), 2, 33, 33), ((8, 8, 3, 1, 11, 1), 1, 40, 24), ((6, 16, 3, 1, 1, 1), 2, 40, 100),
     # past the staged positions: the direct kernel
