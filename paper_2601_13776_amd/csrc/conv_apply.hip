@@ -267,14 +267,17 @@ __global__ __launch_bounds__(256) void conv_apply_kernel(ApplyGeom G, const void
 // Staged rows: consecutive source rows of each image that the tile touches,
 // or (large dilation) k rows per grid row, whichever is fewer.
 //
-// What bounds it: MFMA and the splitting VALU of a SIMD share its issue
-// slots (a chunk of 8 channels with k = 3 costs 1920 cycles of MFMA per wave
-// and about 600 of splitting), and two workgroups per compute unit do not
-// cover each other's barriers fully.  Measured before (fp32 MFMA, staged
-// rows, zero-stuffed transposed form) and now: 256 -> 256 channels, 28 x 28,
-// batch 64: 1017 -> 486 us (58 -> 122 TFLOP/s; bf16 kernel 1066 -> 289);
-// transposed 1004 -> 444; 128 -> 256, stride 2, 32 x 32, batch 128: 394 ->
-// 156 us, transposed 1187 -> 179.
+// What bounds it: six products per fp32 product; 256 channels at 28 x 28 keep
+// the matrix pipes busy 58% of the cycles, at a clock of 1.98 GHz, beside VALU
+// instructions in 34% of the issue cycles; the waves wait 20% of their time
+// for loads and barriers (the transposed form with stride 2, one row tile's
+// four phases: 35%, 31% and 27%, at 2.15 GHz).  Measured with fp32 MFMA and
+// staged rows (the zero-stuffed transposed form) and now: 256 -> 256 channels,
+// 28 x 28, batch 64: 969 -> 387 us (61 -> 153 TFLOP/s; bf16 kernel 1032 ->
+// 243), transposed 998 -> 376 (1158 -> 243); 128 -> 256, stride 2, 32 x 32,
+// batch 128: 389 -> 155 (380 -> 100), transposed 1183 -> 165 (1376 -> 134).
+// With one infinity per sample 984 us and transposed 814, 343 and 722; NaN
+// throughout 458, 396, 225 and 203.
 struct StageGeom {
   int Hg, Wg;            // the grid of the tile's pixels
   int Hs, Ws;            // the source grid

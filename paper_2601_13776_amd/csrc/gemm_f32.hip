@@ -19,16 +19,27 @@
 // 1.3e-7 / 4.0e-7 (one accumulator for all: 1.1e-7 / 3.4e-7 / 1.0e-6).  Two
 // half pieces take half the products, but 22 bits and half's range: light
 // rows and columns beside heavy ones lost theirs.
-// A wave's block with a result that the split cannot give (split_failed: infinities,
-// NaN, overflow, values near the low end of fp32) is computed again with fp32
-// MFMA by the wave that meets it, straight from memory (through LDS, by vote
-// of the workgroup, took 1.80 ms where this takes 1.36, and 0.2 us more of
-// every launch): conv exponentials of 256 channels, 0.89 ms, with one NaN in
-// the kernel 1.36, scaled until they overflow 0.85 (1.23 to 1.34 when every
-// tile ran on fp32 MFMA).
+//
+// A wave's block with a result that the split cannot give (split_failed:
+// infinities, NaN, overflow, values near the low end of fp32) is computed
+// again with fp32 MFMA by the wave that meets it, straight from memory.
+// Conv exponentials of 256 channels: 0.89 ms, 1.36 with one NaN in the kernel
+// (1.23 when every tile ran on fp32 MFMA; a vote of the workgroup and LDS
+// staging took 1.80, and 0.2 us more of every launch).
 //
 // Lists with a 128-tile for every compute unit use those (half the splitting
 // and LDS writes per product), others 64.
+//
+// What bounds it: with 128-tiles (exponential map of 4 x 2048^2) the matrix
+// pipes are busy 53% of the cycles, at a clock of 1.83 GHz, beside VALU
+// instructions (the splitting) in 37% of the issue cycles; the two waves of a
+// SIMD wait 32% of their time for loads and barriers.
+// 64-tile lists have one or two waves a SIMD and pipes that are busy 20 to
+// 26%: one tile's first loads, K loop and epilogue.  Measured with fp32 MFMA
+// and now: exponential map of 4 x 2048^2, 674 -> 410 us per power (102 -> 168
+// TFLOP/s); conv exponential of 512 channels, 1379 -> 849 us per power (100 ->
+// 162); Gram matrix and update of a 2048 x 1024 iterate 65 -> 42 and 59 -> 42
+// us, of eight 512^2 ones 32 -> 22.5 and 36 -> 26.7.
 //
 // K advances in steps of 32 through two LDS stages (see the pipeline below).
 #include "internal.h"

@@ -497,7 +497,10 @@ static_assert(sizeof(GemmItem) % 8 == 0 && sizeof(GemmItem) == 8 * 8 + 14 * 8 + 
               "GemmItem must have no padding: items are compared bytewise");
 // Tile edge of a list whose products make n128 tiles of 128: those halve
 // the LDS traffic and splitting work per product, but a 64-tile list has
-// four times the tiles to fill the 256 compute units with.
+// four times the tiles to fill the 256 compute units with: an update of a
+// 2048 x 1024 iterate (128 tiles of 128) takes 41 us with 64-tiles, 50 with
+// 128-tiles, of a 2048^2 one (256 tiles) 126 and 100; between them they are
+// within 6% (144 to 192 tiles: 128-tiles 3 to 6% faster, 120: 16% slower).
 constexpr int64_t kTile128Min = 256;
 inline int gemm_tile_edge(int64_t n128) { return n128 >= kTile128Min ? 128 : 64; }
 inline int64_t tiles_of(int64_t rows, int edge) { return (rows + edge - 1) / edge; }
