@@ -270,8 +270,8 @@ __global__ __launch_bounds__(256) void conv_apply_kernel(ApplyGeom G, const void
 // What bounds it: six products per fp32 product; 256 channels at 28 x 28 keep
 // the matrix pipes busy 58% of the cycles, at a clock of 1.98 GHz, beside VALU
 // instructions in 34% of the issue cycles; the waves wait 20% of their time
-// for loads and barriers (the transposed form with stride 2, one row tile's
-// four phases: 35%, 31% and 27%, at 2.15 GHz).  Measured with fp32 MFMA and
+// for loads and barriers (the transposed form with stride 2: 34%, 31% and
+// 26%, at 2.15 GHz).  Measured with fp32 MFMA and
 // staged rows (the zero-stuffed transposed form) and now: 256 -> 256 channels,
 // 28 x 28, batch 64: 969 -> 387 us (61 -> 153 TFLOP/s; bf16 kernel 1032 ->
 // 243), transposed 998 -> 376 (1158 -> 243); 128 -> 256, stride 2, 32 x 32,
