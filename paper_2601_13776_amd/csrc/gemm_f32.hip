@@ -141,7 +141,7 @@ __device__ __forceinline__ f32x16 block_f32(const GemmItem& g, const GemmPair* e
     auto load = [&](int k) {
 #pragma unroll
       for (int o = 0; o < 2; ++o) {
-        if (k + 16 <= v.K && ks[o] == 4) {
+        if (k + 16 <= v.K && ks[o] == 4 && !narrow[o]) {
           const uint4 a = gld_u32x4_a4(reinterpret_cast<const float*>(at[o]));
           const uint4 b = gld_u32x4_a4(reinterpret_cast<const float*>(at[o]) + 4);
           w[o][0] = a.x; w[o][1] = a.y; w[o][2] = a.z; w[o][3] = a.w;

@@ -75,6 +75,15 @@ def test_gram_of_bf16(shape, offset):
     assert abs(got - ref) <= TOL * max(1.0, ref)
 
 
+# an infinity in bfloat16 matrices (their blocks run on fp32 products), also
+# where two of them lie in each 4 bytes of a k-major operand
+@pytest.mark.parametrize("shape", [(40, 2), (100, 68), (64, 96)])
+def test_gram_of_bf16_infinite(shape):
+    m = torch.from_numpy(np.abs(_rand(18, *shape)) + 0.1).to(DEV).to(torch.bfloat16)
+    m[3, 1] = float("inf")
+    assert float(orth.orth_check_norm_gram([m])[0]) == float("inf")
+
+
 # light rows keep their own relative accuracy beside rows 2^10 times larger
 def test_row_scales():
     m = _rand(3, 192, 128)
