@@ -632,7 +632,7 @@ __global__ __launch_bounds__(256, 2) void conv_apply_staged_kernel(ApplyGeom G, 
 #pragma unroll
   for (int i = 0; i < NB; ++i) {
     acc[0][i] += acc[1][i];
-    failed |= __any(split_failed(acc[0][i])) ? 1u << i : 0u;
+    failed |= __any(split_failed(acc[0][i], kSplitLo)) ? 1u << i : 0u;
   }
   if (__builtin_expect(failed != 0, 0)) {
 #pragma unroll 1

@@ -462,13 +462,17 @@ __global__ __launch_bounds__(BM == 64 ? 256 : 512, 2) void gemm_f32_kernel(const
   }
 
   // ------------------------------------------------------------ epilogue --
+  // (Series are not asked: a small power comes from operands in range, and one
+  // below 2^-110 loses 2^-134 at most.  Conv exponentials of 256 channels,
+  // entries of 1e-8: 1.90 ms asked, 0.80 not.)
+  const float lo = item.epi == EPI_SERIES ? 0.f : kSplitLo;
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NI; ++j) {
       acc[0][i][j] += acc[1][i][j];
-      bad |= split_failed(acc[0][i][j]);
+      bad |= split_failed(acc[0][i][j], lo);
     }
   if (__builtin_expect(__any(bad), 0)) {
 #pragma unroll 1

@@ -125,11 +125,13 @@ __device__ __forceinline__ void split2_bf16(float a, float b, uint32_t& h, uint3
 
 // Whether split products cannot stand for a lane's 16 results: one is not
 // finite (an infinity splits into inf - inf, a value past bfloat16's largest
-// into an infinity), or the largest is so small (but not zero) that low
-// pieces of its operands may have fallen off the end of bfloat16's range.
-// (Value by value the second test took 0.2 us more of every launch.)
+// into an infinity), or the largest is below `lo` (but not zero): so small
+// that low pieces of its operands may have fallen off the end of bfloat16's
+// range (kSplitLo; 0: not asked).  (Value by value the second test took 0.2
+// us more of every launch.)
+constexpr float kSplitLo = 0x1p-100f;
 template <typename V16>
-__device__ __forceinline__ bool split_failed(const V16& v) {
+__device__ __forceinline__ bool split_failed(const V16& v, float lo) {
   float top = 0.f, nan0 = 0.f, nan1 = 0.f;
 #pragma unroll
   for (int r = 0; r < 16; r += 2) {
@@ -137,7 +139,7 @@ __device__ __forceinline__ bool split_failed(const V16& v) {
     nan0 = fmaf(v[r], 0.f, nan0);
     nan1 = fmaf(v[r + 1], 0.f, nan1);
   }
-  return !(nan0 + nan1 == 0.f) || (top > 0.f && top < 0x1p-100f);
+  return !(nan0 + nan1 == 0.f) || (top > 0.f && top < lo);
 }
 
 template <typename V16>
