@@ -68,9 +68,9 @@ typedef enum { ORTH_F32 = 0, ORTH_BF16 = 1 } orth_dtype;
  * with fp32 accumulation (the iterate itself is always kept in fp32).  fp32
  * operands (here, in the compositions and in the exponentials) enter as
  * three bfloat16 pieces that carry their 24 bits, with fp32 accumulation;
- * blocks with results that are not finite, or not zero and below 2^-100,
- * come from fp32 MFMA.  A value below 2^-110 beside larger ones is exact to
- * 2^-134. */
+ * blocks with results that are not finite, or (but for the exponentials) not
+ * zero and below 2^-100, come from fp32 MFMA.  A value below 2^-110 beside
+ * larger ones, or in a power of an exponential, is exact to 2^-134. */
 typedef enum { ORTH_COMPUTE_F32 = 0, ORTH_COMPUTE_BF16 = 1 } orth_compute;
 
 /* Pre-scaling of W before the iteration: none, W / ||W||_F, or W / sigma

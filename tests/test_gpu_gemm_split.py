@@ -339,3 +339,39 @@ def test_conv_exp_pieces(c, k, terms, scale):
         eye[np.arange(c), np.arange(c), S // 2, S // 2] = 1.0
         off = ~(eye > 0)
         assert checks.relative_difference(got[off][None], ref[off][None]) <= TOL
+
+
+# Blocks that the split cannot give run on fp32 MFMA after it: 16 / 6 of its
+# time at the same efficiency, 3.7 with the first pass.  Calls with one
+# non-finite value among their operands stay within 8 times (an element load
+# per lane and step took 10 to 26 times).
+def _time(f):
+    for _ in range(3):
+        f()
+    e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+    ms = []
+    for _ in range(5):
+        e[0].record()
+        for _ in range(4):
+            f()
+        e[1].record()
+        torch.cuda.synchronize()
+        ms.append(e[0].elapsed_time(e[1]))
+    return sorted(ms)[2]
+
+
+@pytest.mark.parametrize("what", ["conv_exp", "conv", "conv_transposed"])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_cost_of_blocks_computed_again(what, bad):
+    if what == "conv_exp":
+        c, kern = 256, torch.from_numpy(_rand(70, 256, 256, 3, 3) / 48).to(DEV)
+        layer = dict(kernel=kern, out=torch.empty(c, c, 13, 13, device=DEV), terms=6, scale=0.25)
+        hit, run = kern[5, 7, 1], lambda: orth.orth_conv_exp_batched([layer])   # noqa: E731
+    else:
+        geom, tr = (128, 256, 3, 2, 1, 1), what == "conv_transposed"
+        kern = torch.from_numpy(_rand(71, 256, 128, 3, 3) / 34).to(DEV)
+        x = torch.from_numpy(_rand(72, 64, *((256, 16, 16) if tr else (128, 32, 32)))).to(DEV)
+        hit, run = x[:, 3, 2], lambda: orth.orth_conv_apply(kern, geom, x, transposed=tr)   # noqa: E731
+    plain = _time(run)
+    hit[..., 1] = bad
+    assert _time(run) <= 8 * plain
